@@ -162,8 +162,9 @@ int specrouter_verify_attention(const void* q, const void* k_cache, const void* 
  *               unchanged for a sequence with bad data
  * accept_prob, p_tok, q_tok, kl, tv: fp32 [B][gamma_max] or NULL each; entries
  *               j >= gamma_b (and all entries of a bad sequence) are NaN
- * workspace     device scratch of specrouter_accept_workspace_size() bytes; it
- *               must be zero-filled before its FIRST use and every call leaves
+ * workspace     device scratch of specrouter_accept_workspace_size() bytes (part
+ *               of them room for what top-k / top-p keep: with less, such
+ *               calls work through every logit instead); it must be zero-filled before its FIRST use and every call leaves
  *               it zero-filled again, whatever shape the next call has (each
  *               call clears every word it wrote)
  * Logits must be finite or -inf, with |logit| / T < 2^23; a row that is
@@ -212,7 +213,7 @@ int specrouter_accept_and_diverge(const void* p_logits, int64_t p_batch_stride,
  *   strictly larger logits is below top_p (ties kept or dropped together;
  *   the largest logit always stays); 1 is off. top_k < 0 or top_p outside
  *   (0, 1] is SR_EINVAL. With a filter on, one extra kernel finds each row's
- *   threshold first (a radix select over the row); top-p decides on fp32
+ *   threshold first, and what it keeps when that is little; top-p decides on fp32
  *   masses, so a logit whose larger mass is within ~1e-7 of top_p may fall
  *   either way.
  * A NULL sampling pointer means temperature 1. The sampling struct is a host

@@ -67,7 +67,7 @@ int accept_impl(const void* p_logits, int64_t p_batch_stride, const void* q_logi
   return sr::launch_accept(p_logits, p_batch_stride, q_logits, q_batch_stride, logits_dtype,
                            draft_tokens, gamma, u_accept, u_resample, kv_len, accept_len,
                            out_tokens, new_len, accept_prob, p_tok, q_tok, kl, tv, B, gamma_max,
-                           V, temperature, top_k, top_p, rollback, workspace, plan, status,
+                           V, temperature, top_k, top_p, rollback, workspace, workspace_bytes, plan, status,
                            (hipStream_t)stream);
 }
 
@@ -128,9 +128,7 @@ int specrouter_verify_attention(const void* q, const void* k_cache, const void* 
 size_t specrouter_accept_workspace_size(int B, int gamma_max, int V, int logits_dtype) {
   if (B <= 0 || gamma_max < 0 || gamma_max > SPECROUTER_MAX_GAMMA || V <= 0) return 0;
   if (logits_dtype != SR_F32 && logits_dtype != SR_BF16) return 0;
-  sr::AcceptPlan plan;
-  if (sr::accept_plan(B, gamma_max, V, logits_dtype, &plan) != SR_OK) return 0;
-  return plan.workspace_bytes;
+  return sr::accept_workspace_full(B, gamma_max, V, logits_dtype);
 }
 
 int specrouter_accept_and_diverge_sampled(const void* p_logits, int64_t p_batch_stride,

@@ -61,6 +61,11 @@
 // is all zero again when the call ends. The physical length is written by the
 // launch's last finished sequence.
 //
+// With top-k or top-p a kernel before the sweep (filter.inc) finds the rows'
+// thresholds. Rows that keep few entries are "listed" there (the entries of
+// the verifier row and both normalisers in the workspace): the sweep leaves
+// them out and the finish works from the lists, in 64 bits.
+//
 // Greedy decoding (T = 0) runs the same launches with chunk argmaxes in place
 // of the first pass and no TV step or waiting.
 //
@@ -142,6 +147,15 @@ struct RowOut {
 };
 static_assert(sizeof(RowOut) == 32, "RowOut is two 16-byte words");
 
+// A listed row (its kept entries are in the workspace): exponent shift, kept
+// entries (0: none recorded) and their sum.
+struct RowStat {
+  float r;
+  int n;
+  double S;
+};
+static_assert(sizeof(RowStat) == 16, "RowStat is one 16-byte word");
+
 // ---------------------------------------------------------------------------
 // Arguments
 
@@ -171,6 +185,12 @@ struct Args {
   float* xlogit;     // [B][gmax+1][4] the draft token's exponent arguments and shifts, p then q (pair rows)
   float* thr;        // [B][gmax+1][2] top-k / top-p thresholds of the p and q rows, or NULL
   uint32_t* fincnt;  // sequences of this launch finished
+  // rows that top-k / top-p leave few entries of (NULL: no such rows are listed)
+  uint32_t* smask;   // [B] bit j: the sweep takes position j (its rows are not listed)
+  uint32_t* swany;   // non-zero: some bit of smask is set (any launch of the call)
+  RowStat* rowst;    // [B][gmax+1][2] the listed rows, p then q
+  u32x2* lists;      // [B][gmax+1][lcap] the kept entries of the p rows: (value, index), ascending index
+  int lcap;
   int32_t* status;
   // rollback applied as each sequence finishes (rb_kv NULL: none)
   int32_t* rb_kv;            // [B] cache lengths, in/out (this launch's sequences)
@@ -256,8 +276,8 @@ __device__ __forceinline__ RowSpan row_span(const Args& A, int b, int j, bool wi
 }
 
 // Inclusive prefix over sequences of their live-row counts (gamma_b + 1, or 0
-// for an invalid gamma), in LDS.
-__device__ void build_row_table(const int32_t* gamma, int gmax, int B, int* rows) {
+// for an invalid gamma; with smask the rows it names), in LDS.
+__device__ void build_row_table(const int32_t* gamma, const uint32_t* smask, int gmax, int B, int* rows) {
   __shared__ int wsum[kWaves];
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
@@ -266,7 +286,7 @@ __device__ void build_row_table(const int32_t* gamma, int gmax, int B, int* rows
   int run = 0;
   for (int b = b0; b < b1; ++b) {
     const int g = gamma[b];
-    run += (g >= 0 && g <= gmax) ? g + 1 : 0;
+    run += smask ? __popc(smask[b]) : (g >= 0 && g <= gmax) ? g + 1 : 0;
     rows[b] = run;
   }
   const int incl = wave_incl_scan_i(run);
@@ -308,7 +328,13 @@ __device__ void fill_tasks(const Args& A, const int* rows, long n_tasks, int k0,
       else lo = mid + 1;
     }
     const int first = lo ? rows[lo - 1] : 0;
-    const int j = rank - first, gam = rows[lo] - first - 1;
+    int j = rank - first, gam = rows[lo] - first - 1;
+    if (A.smask) {  // the (rank - first)-th row that smask names
+      uint32_t left = A.smask[lo];
+      for (int i = j; i > 0; --i) left &= left - 1u;
+      j = __ffs((int)left) - 1;
+      gam = A.gamma[lo];
+    }
     const int row = lo * (A.gmax + 1) + j;
     tab.pack[tid] = lo | (j << 12) | (gam << 17) | (c << 22);
     tab.x[tid] = j < gam ? A.drafts[(size_t)lo * A.gmax + j] : -1;
@@ -649,6 +675,27 @@ __device__ __forceinline__ void argmax_pass(const Args& A, const TaskInfo& t, co
   }
 }
 
+// An entry of a listed row: the exponent argument x = z lg - r rounded to 32
+// bits, its exponential, and what the rounding of x left out (the whole row
+// shares one shift, so x of a small entry is rounded coarsely; the correction
+// to first order leaves the exponential's own error, about 1e-7).
+struct ListEnt {
+  float x, e;
+  double d;
+  __device__ __forceinline__ ListEnt(float z, float lg, float r) {
+    x = fmaf(z, lg, -r);
+    e = exp2_hw(x);
+    d = fma((double)z, (double)lg, -(double)r) - (double)x;
+  }
+  __device__ __forceinline__ double val() const { return fma((double)e, kLn2 * d, (double)e); }
+};
+
+// A row that is not listed: the sweep takes position j of sequence b.
+__device__ __forceinline__ void to_sweep(const Args& A, int b, int j) {
+  atomicOr(&A.smask[b], 1u << j);
+  *A.swany = 1u;
+}
+
 // ---------------------------------------------------------------------------
 // Row merges (one wave; the same code wherever a row is merged, so every
 // merge of a row gives the same bits)
@@ -901,19 +948,33 @@ __device__ void count_finished(const Args& A, uint32_t n) {
 // Zero every workspace word sequence b's rows used, so the workspace is all
 // zero again when the call ends: the next call, whatever its shape, lays its
 // regions over these bytes, and its polls take any non-zero record word for a
-// published one.
-__device__ void clear_sequence(const Args& A, int b, int gam) {
+// published one. (One wave; clear_lists the listed rows, every wave.)
+__device__ void clear_sequence(const Args& A, int b, int gam, bool swept) {
   const int lane = threadIdx.x & 63;
   const size_t r0 = (size_t)b * (A.gmax + 1);
+  if (A.thr)
+    for (int i = lane; i < 2 * (gam + 1); i += 64) A.thr[r0 * 2 + i] = 0.f;
+  if (!swept) return;  // every row was listed: the sweep wrote nothing
   const u32x4 z4 = u32x4{0u, 0u, 0u, 0u};
   // the records with device-coherent stores
   const uint32_t nrec = (uint32_t)((gam + 1) * A.nc * 2);  // 16-byte words
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(A.recs + r0 * A.nc * 2, (size_t)nrec * 16);
   for (uint32_t i = lane; i < nrec; i += 64) __builtin_amdgcn_raw_buffer_store_b128(z4, rs, i * 16u, 0, kDeviceCoherent);
   for (size_t i = lane; i < (size_t)gam * A.nc * kWaves; i += 64) A.tva[r0 * A.nc * kWaves + i] = 0.0;
-  for (int i = lane; i < 2 * (gam + 1); i += 64)
-    if (A.thr) A.thr[r0 * 2 + i] = 0.f;
   for (int i = lane; i < 4 * gam; i += 64) A.xlogit[r0 * 4 + i] = 0.f;
+}
+__device__ __forceinline__ void clear_lists(const Args& A, int b, int gam) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  for (int j = w; j <= gam; j += kFinWaves) {
+    const size_t row = (size_t)b * (A.gmax + 1) + j;
+    const int n = A.rowst[row * 2].n;
+    for (int i = lane; i < n; i += 64) A.lists[row * A.lcap + i] = u32x2{0u, 0u};
+    if (lane < 2) A.rowst[row * 2 + lane] = RowStat{0.f, 0, 0.0};
+  }
+  if (threadIdx.x == 0) {
+    A.smask[b] = 0u;
+    *A.swany = 0u;  // (only the sweep, which is over, reads it)
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1324,6 +1385,190 @@ __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amd
 }
 
 // ---------------------------------------------------------------------------
+// Listed rows (top-k / top-p left few entries of them)
+
+// Raw logit x of a row (any alignment).
+template <bool BF16>
+__device__ __forceinline__ float logit_at(const void* base, int64_t off, int x) {
+  if constexpr (BF16) return __uint_as_float((uint32_t)((const uint16_t*)base)[off + x] << 16);
+  else return ((const float*)base)[off + x];
+}
+
+// An entry's probabilities under the row's filtered p and q, from its raw
+// logits (q's is 0 where its filter dropped the entry).
+struct ListRow {
+  RowStat p, q;
+  float thp, thq;
+  double ip, iq;  // 1 / S
+  bool pair;
+};
+template <bool BF16>
+__device__ __forceinline__ ListRow list_row(const Args& A, int row, bool pair) {
+  ListRow L;
+  L.pair = pair;
+  L.p = A.rowst[(size_t)row * 2];
+  L.q = pair ? A.rowst[(size_t)row * 2 + 1] : RowStat{0.f, 0, 1.0};
+  L.thp = A.thr[(size_t)row * 2];
+  L.thq = pair ? A.thr[(size_t)row * 2 + 1] : 0.f;
+  L.ip = 1.0 / L.p.S;
+  L.iq = 1.0 / L.q.S;
+  return L;
+}
+
+// Row j of sequence b (one wave) from its list: TV, KL, p(x), q(x) and a, all
+// in 64 bits. The p row's kept entries come from the list, q's logits at the
+// same places from memory; what q keeps elsewhere is its sum less what was met.
+template <bool BF16>
+__device__ RowOut finalize_listed(const Args& A, int b, int j, int gam) {
+  const int lane = threadIdx.x & 63;
+  const int row = b * (A.gmax + 1) + j;
+  const float nan = __builtin_nanf("");
+  RowOut o;
+  o.pad = 0;
+  o.argp = -1;
+  o.a = 0.0;
+  o.p_tok = o.q_tok = o.kl = o.tv = nan;
+  if (j >= gam) return o;
+  const int64_t po = (int64_t)b * A.p_stride + (int64_t)j * A.V, qo = (int64_t)b * A.q_stride + (int64_t)j * A.V;
+  const int x = A.drafts[(size_t)b * A.gmax + j];
+  const bool xin = x >= 0 && x < A.V;
+  const float zxp = logit_at<BF16>(A.p, po, xin ? x : 0), zxq = logit_at<BF16>(A.q, qo, xin ? x : 0);
+  const ListRow L = list_row<BF16>(A, row, true);
+  const u32x2* list = A.lists + (size_t)row * A.lcap;
+  constexpr int U = 4;  // entries in flight per lane
+  double tv = 0.0, kl = 0.0, mass = 0.0, qsum = 0.0;
+  int met = 0;
+  for (int i0 = 0; i0 < L.p.n; i0 += 64 * U) {
+    u32x2 e[U];
+    float zq[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = list[min(i0 + u * 64 + lane, L.p.n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) zq[u] = logit_at<BF16>(A.q, qo, (int)e[u][1]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * 64 + lane < L.p.n) {
+        const ListEnt p(__uint_as_float(e[u][0]), A.lg, L.p.r), q(zq[u], A.lg, L.q.r);
+        const double P = p.val() * L.ip;
+        const bool both = zq[u] >= L.thq;
+        const double eq = both ? q.val() : 0.0;
+        tv += fabs(P - eq * L.iq);
+        // P (x_p - x_q), the product of the rounded arguments as the sweep forms it
+        if (P > 0.0)
+          kl += both ? fma(kLn2, p.d, 1.0) * (double)(p.e * (p.x - q.x)) * L.ip + P * (p.d - q.d) : (double)__builtin_inff();
+        mass += P;
+        qsum += eq;
+        met += both ? 1 : 0;
+      }
+    }
+  }
+  tv = wave_sum_d(tv);
+  kl = wave_sum_d(kl);
+  mass = wave_sum_d(mass);
+  qsum = wave_sum_d(qsum);
+  for (int d = 1; d < 64; d <<= 1) met += __shfl_xor(met, d, 64);
+  const double rest = met == L.q.n ? 0.0 : fmax(0.0, L.q.S - qsum) * L.iq;  // what q keeps and p does not
+  o.tv = (float)(0.5 * (tv + rest));
+  o.kl = (float)(kLn2 * kl - log(L.p.S / L.q.S) * mass);
+  if (xin) {
+    const double px = zxp >= L.thp ? ListEnt(zxp, A.lg, L.p.r).val() * L.ip : 0.0;
+    const double qx = zxq >= L.thq ? ListEnt(zxq, A.lg, L.q.r).val() * L.iq : 0.0;
+    o.a = (qx == 0.0 || px >= qx) ? 1.0 : px / qx;
+    o.p_tok = (float)px;
+    o.q_tok = (float)qx;
+  } else {
+    o.a = __builtin_nan("");
+  }
+  return o;
+}
+
+// What the draw from a listed row shares.
+struct ListDraw {
+  double res[kFinWaves], p[kFinWaves];
+  int hit[kFinWaves], last[kFinWaves];
+};
+
+// The draw at listed row k (every wave of the workgroup calls it; the token is
+// valid in all): the row's entries in index order, kListPer consecutive ones per
+// thread, weighed by the residual if it has mass, else by p.
+constexpr int kListMax = 2048;  // entries of a list at most
+constexpr int kListPer = kListMax / (64 * kFinWaves);
+template <bool BF16>
+__device__ int draw_listed(const Args& A, int b, int k, int gam, float u, ListDraw& ds) {
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
+  const int row = b * (A.gmax + 1) + k;
+  const bool pair = k < gam;
+  const ListRow L = list_row<BF16>(A, row, pair);
+  const int per = (L.p.n + 64 * kFinWaves - 1) / (64 * kFinWaves);
+  const int i0 = tid * per;
+  const u32x2* list = A.lists + (size_t)row * A.lcap;
+  const int64_t qo = (int64_t)b * A.q_stride + (int64_t)k * A.V;
+  u32x2 e[kListPer];
+  float zq[kListPer];
+#pragma unroll
+  for (int i = 0; i < kListPer; ++i) e[i] = list[min(i0 + min(i, per - 1), L.p.n - 1)];
+#pragma unroll
+  for (int i = 0; i < kListPer; ++i) zq[i] = pair ? logit_at<BF16>(A.q, qo, (int)e[i][1]) : kNegInf;
+  double wr[kListPer], wp[kListPer], sr = 0.0, sp = 0.0;
+#pragma unroll
+  for (int i = 0; i < kListPer; ++i) {
+    const bool in = i < per && i0 + i < L.p.n;
+    const double P = in ? ListEnt(__uint_as_float(e[i][0]), A.lg, L.p.r).val() * L.ip : 0.0;
+    const double Q = in && pair && zq[i] >= L.thq ? ListEnt(zq[i], A.lg, L.q.r).val() * L.iq : 0.0;
+    wp[i] = P;
+    wr[i] = pair ? fmax(0.0, P - Q) : 0.0;
+    sp += wp[i];
+    sr += wr[i];
+  }
+  const double ir = wave_incl_scan_d(sr), ip = wave_incl_scan_d(sp);
+  if (lane == 63) {
+    ds.res[w] = ir;
+    ds.p[w] = ip;
+  }
+  __syncthreads();
+  double tr = 0.0, tp = 0.0, br = 0.0, bp = 0.0;
+  for (int i = 0; i < kFinWaves; ++i) {
+    if (i == w) {
+      br = tr;
+      bp = tp;
+    }
+    tr += ds.res[i];
+    tp += ds.p[i];
+  }
+  const bool resid = tr > 0.0;
+  const double target = (double)u * (resid ? tr : tp);
+  const double mine = resid ? sr : sp;
+  const double incl = resid ? br + ir : bp + ip;
+  // the first thread whose end exceeds the target, and the last entry with weight
+  const unsigned long long h = __ballot(incl > target && mine > 0.0);
+  double run = incl - mine;
+  int found = -1, last = -1;
+#pragma unroll
+  for (int i = 0; i < kListPer; ++i) {
+    const double wi = resid ? wr[i] : wp[i];
+    run += wi;
+    if (wi > 0.0) {
+      last = (int)e[i][1];
+      if (found < 0 && run > target) found = last;
+    }
+  }
+  if (found < 0) found = last;
+  const int wl = wave_max_i(last);
+  const int tok_h = h ? __builtin_amdgcn_readlane(found, __ffsll((long long)h) - 1) : -1;
+  if (lane == 0) {
+    ds.hit[w] = tok_h;
+    ds.last[w] = wl;
+  }
+  __syncthreads();
+  int tok = -1, end = -1;
+  for (int i = 0; i < kFinWaves; ++i) {
+    if (tok < 0) tok = ds.hit[i];
+    end = max(end, ds.last[i]);
+  }
+  return tok >= 0 ? tok : end < 0 ? 0 : end;  // (rounding put the target at the very end)
+}
+
+// ---------------------------------------------------------------------------
 // Sequence finisher (one wave)
 
 // A sequence's per-position inputs as wave 0 holds them (lane j: position j),
@@ -1357,19 +1602,23 @@ __device__ __forceinline__ SeqIn load_seq_inputs(const Args& A, int b, int gam) 
 
 // What the finisher's waves share.
 struct FinShared {
-  DrawShared ds;
+  union {
+    DrawShared ds;
+    ListDraw ld;
+  };
   uint32_t bits;
   int k;
+  float u;  // u_res[k]
 };
 
 // The sequence's outcome (every wave of the workgroup calls it): wave 0 reads
 // the per-position inputs, checks them and runs the accept chain; the first
 // four waves scan the stopping row's chunk for the drawn token (greedy: the
-// row's argmax); wave 0 writes the outputs and the rollback while the last
+// row's argmax; a listed row: every wave scans its list); wave 0 writes the outputs and the rollback while the last
 // wave zeroes the sequence's workspace words.
-template <bool BF16, bool GREEDY>
+template <bool BF16, bool GREEDY, bool LIST>
 __device__ void finish_sequence(const Args& A, int b, int gam, const RowOut* rows, const DrawPlan* plans,
-                                const SeqIn& in, FinShared& fs) {
+                                const SeqIn& in, uint32_t swept, FinShared& fs) {
   const int lane = threadIdx.x & 63, w = wave_id();
   const int G1 = A.gmax + 1;
   int x = -1;
@@ -1406,9 +1655,11 @@ __device__ void finish_sequence(const Args& A, int b, int gam, const RowOut* row
     // the accept chain
     const bool rej = lane < gam && (GREEDY ? x != argp : !((double)ua < a));
     const unsigned long long rmask = __ballot(rej);
-    if (lane == 0) {
+    const int kk = rmask ? (__ffsll((long long)rmask) - 1) : gam;
+    if (lane == kk) {
       fs.bits = bits;
-      fs.k = rmask ? (__ffsll((long long)rmask) - 1) : gam;
+      fs.k = kk;
+      fs.u = ur;
     }
   }
   __syncthreads();
@@ -1417,9 +1668,11 @@ __device__ void finish_sequence(const Args& A, int b, int gam, const RowOut* row
   int tok = 0;
   if (!bits) {  // workgroup-uniform
     if constexpr (GREEDY) tok = rows[k].argp;
-    else tok = draw_scan<BF16>(A, b, k, plans[k], fs.ds);
+    else if (!LIST || ((swept >> k) & 1u)) tok = draw_scan<BF16>(A, b, k, plans[k], fs.ds);
+    else tok = draw_listed<BF16>(A, b, k, gam, fs.u, fs.ld);
   }
-  if (w == kFinWaves - 1) clear_sequence(A, b, gam);
+  if constexpr (LIST) clear_lists(A, b, gam);  // (behind the barriers above: every wave has read the lists)
+  if (w == kFinWaves - 1) clear_sequence(A, b, gam, swept != 0u);
   if (w != 0) return;
   if (bits) {
     write_invalid(A, b, bits);
@@ -1523,7 +1776,8 @@ __global__ void __launch_bounds__(kThreads, 2) accept_kernel(Args A) {
   extern __shared__ int s_rows[];  // [B] inclusive prefix of live rows
   __shared__ TaskShared sh;
   __shared__ TaskTable tab;
-  build_row_table(A.gamma, A.gmax, A.B, s_rows);
+  if (!GREEDY && A.smask && *A.swany == 0u) return;  // every row is listed
+  build_row_table(A.gamma, A.smask, A.gmax, A.B, s_rows);
   const long n_tasks = (long)s_rows[A.B - 1] * A.nc;
   if (blockIdx.x >= n_tasks) return;
   const int n_my = (int)((n_tasks - blockIdx.x + gridDim.x - 1) / gridDim.x);  // this workgroup's tasks
@@ -1554,9 +1808,10 @@ __global__ void __launch_bounds__(kThreads, 2) accept_kernel(Args A) {
 // finalise the sequence's rows (wave w takes rows w, w + 8, ...) into LDS,
 // each with the plan of the draw the sequence would make if it stopped there;
 // then the sequence's outcome (finish_sequence). A sequence with gamma
-// outside [0, gamma_max] gets the invalid outputs.
+// outside [0, gamma_max] gets the invalid outputs. LIST: rows may be listed
+// (a kernel of its own: the lists' registers stay out of the plain one).
 
-template <bool BF16, bool GREEDY>
+template <bool BF16, bool GREEDY, bool LIST>
 __global__ void __launch_bounds__(64 * kFinWaves) accept_finish_kernel(Args A) {
   __shared__ RowOut s_out[kMaxRows];
   __shared__ DrawPlan s_plan[kMaxRows];
@@ -1573,8 +1828,16 @@ __global__ void __launch_bounds__(64 * kFinWaves) accept_finish_kernel(Args A) {
   }
   SeqIn in;
   if (w == 0) in = load_seq_inputs<GREEDY>(A, b, gam);
+  const uint32_t swept = LIST ? A.smask[b] : 0xffffffffu;  // bit j: row j came through the sweep
   const __amdgpu_buffer_rsrc_t rs_recs = make_rsrc(A.recs, (size_t)A.B * (A.gmax + 1) * A.nc * kRecBytes);
   for (int j = w; j <= gam; j += kFinWaves) {
+    if constexpr (LIST) {
+      if (!((swept >> j) & 1u)) {
+        const RowOut o = finalize_listed<BF16>(A, b, j, gam);
+        if (lane == 0) s_out[j] = o;
+        continue;
+      }
+    }
     DrawPlan plan;
     const RowOut o = finalize_row<BF16, GREEDY>(A, b, j, gam, rs_recs, plan);
     if (lane == 0) {
@@ -1583,7 +1846,7 @@ __global__ void __launch_bounds__(64 * kFinWaves) accept_finish_kernel(Args A) {
     }
   }
   __syncthreads();
-  finish_sequence<BF16, GREEDY>(A, b, gam, s_out, s_plan, in, fs);
+  finish_sequence<BF16, GREEDY, LIST>(A, b, gam, s_out, s_plan, in, swept, fs);
 }
 
 // ============================================================================
@@ -1649,7 +1912,46 @@ int persistent_grid(const void* fn, long max_tasks, int Bl, int nc) {
   return grid < 1 ? 1 : (int)grid;
 }
 
+
+// What listing filtered rows takes behind the rest of the workspace: the mask
+// of swept rows, the row records, and lists of lcap entries per verifier row.
+// A list holds up to an eighth of the vocabulary, at most kListMax entries
+// (nucleus 0.9 of 128256 logits N(0, 9) at T = 0.7 keeps 400 to 750), and all
+// together keep the workspace within the fixed array of the no-allocation
+// call where the rest of it does, so that call takes the same shapes as
+// without lists and gives the same bits as a call with a workspace.
+struct ListLayout {
+  size_t smask, rowst, lists, total;
+  int lcap;  // 0: no room, no lists
+};
+
+ListLayout list_layout(int B, int gamma_max, int V, size_t base) {
+  const size_t rows = (size_t)B * (gamma_max + 1);
+  ListLayout L;
+  L.smask = base;
+  L.rowst = L.smask + align256(((size_t)B + 1) * sizeof(uint32_t));
+  L.lists = L.rowst + align256(rows * 2 * sizeof(RowStat));
+  size_t cap = (size_t)((V / 8 + 63) / 64 * 64);
+  if (cap < 64) cap = 64;
+  if (cap > (size_t)kListMax) cap = kListMax;
+  if (base <= SPECROUTER_NOALLOC_SCRATCH_BYTES) {
+    const size_t left = SPECROUTER_NOALLOC_SCRATCH_BYTES > L.lists + 256 ? SPECROUTER_NOALLOC_SCRATCH_BYTES - L.lists - 256 : 0;
+    const size_t fit = left / (rows * sizeof(u32x2)) / 64 * 64;
+    if (fit < cap) cap = fit;
+  } else if (cap > 512) {
+    cap = 512;  // a very large batch: 4 KB per verifier row
+  }
+  L.lcap = (int)cap;
+  L.total = cap ? L.lists + align256(rows * cap * sizeof(u32x2)) : base;
+  return L;
+}
+
 }  // namespace
+
+size_t accept_workspace_full(int B, int gamma_max, int V, int dtype) {
+  const size_t base = accept_workspace_bytes(B, gamma_max, V, dtype);
+  return base == 0 ? 0 : list_layout(B, gamma_max, V, base).total;
+}
 
 size_t accept_workspace_bytes(int B, int gamma_max, int V, int dtype) {
   if (B <= 0 || gamma_max < 0 || gamma_max > SPECROUTER_MAX_GAMMA || V <= 0) return 0;
@@ -1674,7 +1976,7 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
                   int32_t* out_tokens, int32_t* new_len, float* accept_prob, float* p_tok,
                   float* q_tok, float* kl, float* tv, int B, int gamma_max, int V, float temperature,
                   int top_k, float top_p, const AcceptRollback* rollback, void* workspace,
-                  const AcceptPlan& plan, int32_t* status, hipStream_t stream) {
+                  size_t workspace_bytes, const AcceptPlan& plan, int32_t* status, hipStream_t stream) {
   const int nc = plan.n_chunks;
   const Layout L = layout(B, gamma_max, nc);
   const bool greedy = temperature == 0.f;
@@ -1685,6 +1987,9 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
   const int k_eff = top_k > 0 && top_k < V ? top_k : 0;
   const float p_eff = top_p < 1.f ? top_p : 1.f;
   const bool filt = !greedy && (k_eff > 0 || p_eff < 1.f);
+  // rows are listed when the workspace has the room that its size query asks for
+  const ListLayout LL = list_layout(B, gamma_max, V, plan.workspace_bytes);
+  const bool list = filt && LL.lcap > 0 && workspace_bytes >= LL.total;
   // sequences in launches of at most kMaxSeqs (the row table)
   for (int b0 = 0; b0 < B; b0 += kMaxSeqs) {
     const int Bl = B - b0 < kMaxSeqs ? B - b0 : kMaxSeqs;
@@ -1717,6 +2022,11 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     A.xlogit = (float*)(ws + L.xlogit) + r0 * 4;
     A.thr = filt ? (float*)(ws + L.thr) + r0 * 2 : nullptr;
     A.fincnt = (uint32_t*)(ws + L.fincnt);
+    A.smask = list ? (uint32_t*)(ws + LL.smask) + b0 : nullptr;
+    A.swany = list ? (uint32_t*)(ws + LL.smask) + B : nullptr;
+    A.rowst = list ? (RowStat*)(ws + LL.rowst) + r0 * 2 : nullptr;
+    A.lists = list ? (u32x2*)(ws + LL.lists) + r0 * LL.lcap : nullptr;
+    A.lcap = list ? LL.lcap : 0;
     A.status = status;
     A.rb_kv = rollback ? rollback->kv_len + b0 : nullptr;
     A.rb_mask = rollback && rollback->mask ? rollback->mask + (size_t)b0 * rollback->L_cap : nullptr;
@@ -1732,18 +2042,16 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     const size_t lds = Bl * sizeof(int);  // the row table
     if (filt) {  // the rows' top-k / top-p thresholds first
       const dim3 grid_f((unsigned)(Bl * (2 * G1 - 1)));
+      typedef void (*Filter)(Args, int, float);
+      const bool bf = dtype == SR_BF16, mass = k_eff == 0;  // (mass: top-p alone)
       if ((long)grid_f.x >= 2L * device_cu_count()) {
-        const dim3 blk(filt512::kFiltThreads);
-        if (dtype == SR_BF16)
-          hipLaunchKernelGGL(filt512::accept_filter_kernel<true>, grid_f, blk, 0, stream, A, k_eff, p_eff);
-        else
-          hipLaunchKernelGGL(filt512::accept_filter_kernel<false>, grid_f, blk, 0, stream, A, k_eff, p_eff);
+        const Filter fn = bf ? (mass ? filt512::accept_filter_kernel<true, true> : filt512::accept_filter_kernel<true, false>)
+                             : (mass ? filt512::accept_filter_kernel<false, true> : filt512::accept_filter_kernel<false, false>);
+        hipLaunchKernelGGL(fn, grid_f, dim3(filt512::kFiltThreads), 0, stream, A, k_eff, p_eff);
       } else {
-        const dim3 blk(filt1024::kFiltThreads);
-        if (dtype == SR_BF16)
-          hipLaunchKernelGGL(filt1024::accept_filter_kernel<true>, grid_f, blk, 0, stream, A, k_eff, p_eff);
-        else
-          hipLaunchKernelGGL(filt1024::accept_filter_kernel<false>, grid_f, blk, 0, stream, A, k_eff, p_eff);
+        const Filter fn = bf ? (mass ? filt1024::accept_filter_kernel<true, true> : filt1024::accept_filter_kernel<true, false>)
+                             : (mass ? filt1024::accept_filter_kernel<false, true> : filt1024::accept_filter_kernel<false, false>);
+        hipLaunchKernelGGL(fn, grid_f, dim3(filt1024::kFiltThreads), 0, stream, A, k_eff, p_eff);
       }
       if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
     }
@@ -1758,11 +2066,13 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
     const dim3 grid_s((unsigned)Bl), block_s(64 * kFinWaves);
     if (dtype == SR_BF16) {
-      if (greedy) hipLaunchKernelGGL((accept_finish_kernel<true, true>), grid_s, block_s, 0, stream, A);
-      else hipLaunchKernelGGL((accept_finish_kernel<true, false>), grid_s, block_s, 0, stream, A);
+      if (greedy) hipLaunchKernelGGL((accept_finish_kernel<true, true, false>), grid_s, block_s, 0, stream, A);
+      else if (list) hipLaunchKernelGGL((accept_finish_kernel<true, false, true>), grid_s, block_s, 0, stream, A);
+      else hipLaunchKernelGGL((accept_finish_kernel<true, false, false>), grid_s, block_s, 0, stream, A);
     } else {
-      if (greedy) hipLaunchKernelGGL((accept_finish_kernel<false, true>), grid_s, block_s, 0, stream, A);
-      else hipLaunchKernelGGL((accept_finish_kernel<false, false>), grid_s, block_s, 0, stream, A);
+      if (greedy) hipLaunchKernelGGL((accept_finish_kernel<false, true, false>), grid_s, block_s, 0, stream, A);
+      else if (list) hipLaunchKernelGGL((accept_finish_kernel<false, false, true>), grid_s, block_s, 0, stream, A);
+      else hipLaunchKernelGGL((accept_finish_kernel<false, false, false>), grid_s, block_s, 0, stream, A);
     }
     if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
   }

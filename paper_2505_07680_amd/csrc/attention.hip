@@ -46,7 +46,6 @@ namespace sr {
 namespace {
 
 typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWaves = 4;  // key streams

@@ -11,6 +11,7 @@ namespace sr {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_inff();
@@ -78,6 +79,13 @@ __device__ __forceinline__ float opaque_inf() {
   return r;
 }
 __device__ __forceinline__ float max_nn(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, opaque_inf()); }
+
+// max(a, b, c) for non-NaN operands: one instruction, no quieting.
+__device__ __forceinline__ float max3_nn(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
 
 // (value of the even row, value of the odd row) of each pair of 16-lane rows,
 // in every lane; with kHalf32 the same for the two 32-lane halves.
@@ -284,8 +292,10 @@ struct AcceptPlan {
 
 int accept_plan(int B, int gamma_max, int V, int dtype, AcceptPlan* plan);
 // The workspace bytes an accept call of this shape needs (0: unsupported
-// shape); host arithmetic only, no device query.
+// shape), and those with which filtered rows can be listed (at least as
+// many); host arithmetic only, no device query.
 size_t accept_workspace_bytes(int B, int gamma_max, int V, int dtype);
+size_t accept_workspace_full(int B, int gamma_max, int V, int dtype);
 
 // Rollback applied by the accept call itself (after each sequence's outcome):
 // the same update as launch_rollback with new_len = the accept's new length.
@@ -302,7 +312,7 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
                   int32_t* out_tokens, int32_t* new_len, float* accept_prob, float* p_tok,
                   float* q_tok, float* kl, float* tv, int B, int gamma_max, int V, float temperature,
                   int top_k, float top_p, const AcceptRollback* rollback, void* workspace,
-                  const AcceptPlan& plan, int32_t* status, hipStream_t stream);
+                  size_t workspace_bytes, const AcceptPlan& plan, int32_t* status, hipStream_t stream);
 
 int launch_chain_window(const int32_t* accept_len, const int32_t* out_tokens, int B, int gmax, int cap,
                         const int32_t* ctx_len, int32_t* gamma_next, int32_t* drafts_next,
