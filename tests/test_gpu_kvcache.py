@@ -95,6 +95,42 @@ def test_compact_matches_reference(D):
     np.testing.assert_array_equal(host(vd).view(np.uint16), rv)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L_cap", [1, 127, 128, 129, 385, 1027])
+def test_compact_at_block_edges(D, L_cap):
+    """Lengths around the 128-position blocks, holes only in some blocks (a
+    whole block of holes, a single hole at a block's first or last position,
+    only the last row valid), and mask rows at every alignment (odd L_cap)."""
+    import paper_2505_07680_amd as sr
+
+    rng = np.random.default_rng(L_cap * 2 + D)
+    B, Hkv = 8, 2
+    k, v = _bits(rng, (B, Hkv, L_cap, D)), _bits(rng, (B, Hkv, L_cap, D))
+    kv_len = np.full(B, L_cap, np.int32)
+    kv_len[1] = min(L_cap, 128)
+    kv_len[2] = max(L_cap - 1, 0)
+    mask = np.ones((B, L_cap), np.uint8)
+    mask[0, :128] = 0                      # a whole block
+    mask[1, : min(127, L_cap - 1)] = 0     # only the last row of the block
+    mask[2, min(127, L_cap - 1)] = 0       # a block's last position
+    mask[3, min(128, L_cap - 1)] = 0       # a block's first position
+    mask[4, :-1] = 0                       # only the last row
+    mask[5] = rng.random(L_cap) < 0.5
+    mask[6, 128:256] = 0
+    mask[7] *= 3                           # any non-zero byte is valid
+    mask[7, ::3] = 0
+    kd, vd, md, ld = dev(k), dev(v), dev(mask), dev(kv_len)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    say(f"kv compact edges D={D} L_cap={L_cap}")
+    sr.specrouter_kv_compact(kd, vd, md, ld, st)
+    rk, rv, rm, rl, rst = kvcache.compact(k, v, mask, kv_len)
+    assert int(host(st)[0]) == rst == 0
+    np.testing.assert_array_equal(host(ld), rl)
+    np.testing.assert_array_equal(host(md), rm)
+    np.testing.assert_array_equal(host(kd).view(np.uint16), rk)
+    np.testing.assert_array_equal(host(vd).view(np.uint16), rv)
+
+
 def test_paper_layout_cycle_on_device():
     """Shared physical length, paper-shaped attention (MHA, 32 heads)."""
     import paper_2505_07680_amd as sr
