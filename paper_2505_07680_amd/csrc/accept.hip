@@ -93,8 +93,10 @@ namespace {
 constexpr int kThreads = 256;  // four waves, one task
 constexpr int kWaves = kThreads / 64;
 constexpr int kFinWaves = 8;  // waves of a finish workgroup
-constexpr int kSlots = 2;               // chunk records per lane in a row merge
-constexpr int kMaxChunks = 64 * kSlots; // per row
+// Chunk records per lane in a row merge (NS below): one up to 64 chunks per row
+// (V up to about 262000), else two.
+constexpr int kMaxSlots = 2;
+constexpr int kMaxChunks = 64 * kMaxSlots;  // per row
 constexpr int kMaxRows = SPECROUTER_MAX_GAMMA + 1;
 constexpr int kMaxSeqs = 4096;               // sequences per launch (row table in LDS)
 constexpr int kDeviceCoherent = 16;          // buffer cache-policy operand: sc1
@@ -300,7 +302,7 @@ __device__ void build_row_table(const int32_t* gamma, const uint32_t* smask, int
 
 struct TaskInfo {
   int b, j, c, row, x, gam, phi;
-  float thp, thq;  // the row's top-k / top-p thresholds (read only when A.thr is set)
+  float thp, thq;  // the row's top-k / top-p thresholds (FILT)
   bool pair, full;
 };
 
@@ -316,6 +318,7 @@ struct TaskTable {
 };
 
 // Tasks k0 .. k0 + kTab - 1 of this workgroup (task blockIdx.x + k * gridDim.x).
+template <bool FILT>
 __device__ void fill_tasks(const Args& A, const int* rows, long n_tasks, int k0, TaskTable& tab) {
   const int tid = threadIdx.x;
   const long task = blockIdx.x + (long)(k0 + tid) * gridDim.x;
@@ -329,7 +332,7 @@ __device__ void fill_tasks(const Args& A, const int* rows, long n_tasks, int k0,
     }
     const int first = lo ? rows[lo - 1] : 0;
     int j = rank - first, gam = rows[lo] - first - 1;
-    if (A.smask) {  // the (rank - first)-th row that smask names
+    if (FILT && A.smask) {  // the (rank - first)-th row that smask names
       uint32_t left = A.smask[lo];
       for (int i = j; i > 0; --i) left &= left - 1u;
       j = __ffs((int)left) - 1;
@@ -338,13 +341,15 @@ __device__ void fill_tasks(const Args& A, const int* rows, long n_tasks, int k0,
     const int row = lo * (A.gmax + 1) + j;
     tab.pack[tid] = lo | (j << 12) | (gam << 17) | (c << 22);
     tab.x[tid] = j < gam ? A.drafts[(size_t)lo * A.gmax + j] : -1;
-    tab.thp[tid] = A.thr ? A.thr[(size_t)row * 2] : kNegInf;
-    tab.thq[tid] = A.thr && j < gam ? A.thr[(size_t)row * 2 + 1] : kNegInf;
+    if constexpr (FILT) {
+      tab.thp[tid] = A.thr[(size_t)row * 2];
+      tab.thq[tid] = j < gam ? A.thr[(size_t)row * 2 + 1] : kNegInf;
+    }
   }
   __syncthreads();
 }
 
-template <bool BF16>
+template <bool BF16, bool FILT>
 __device__ __forceinline__ TaskInfo decode_task(const Args& A, const TaskTable& tab, int k) {
   TaskInfo t;
   const int i = k % kTab;
@@ -359,8 +364,11 @@ __device__ __forceinline__ TaskInfo decode_task(const Args& A, const TaskTable& 
   constexpr int kChunk = Vec<BF16>::kChunk;
   t.full = t.c * kChunk >= t.phi && (t.c + 1) * kChunk <= t.phi + A.V;
   t.x = __builtin_amdgcn_readfirstlane(tab.x[i]);
-  t.thp = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tab.thp[i])));
-  t.thq = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tab.thq[i])));
+  t.thp = t.thq = kNegInf;
+  if constexpr (FILT) {
+    t.thp = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tab.thp[i])));
+    t.thq = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tab.thq[i])));
+  }
   return t;
 }
 
@@ -400,6 +408,63 @@ template <int kE>
 __device__ __forceinline__ void mask_below(float (&z)[kE], float t) {
 #pragma unroll
   for (int e = 0; e < kE; ++e) z[e] = z[e] >= t ? z[e] : kNegInf;
+}
+
+// Wave totals in scalar registers (a fixed tree: within rows of 16 lanes by
+// shifts, then the rows in order), one instruction per step and value: lane
+// 63 ends with the total. The waits between a step and the next one's DPP read
+// (two instructions) are the other values' steps, or s_nop.
+#define SR_SUM_STEPS(step, wait)                                                                                     \
+  "s_nop 1\n\t" step("row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0") wait                                       \
+      step("row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:0") wait                                                 \
+      step("row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:0") wait                                                 \
+      step("row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:0") wait                                                 \
+      step("row_bcast:15 row_mask:0xa bank_mask:0xf") wait step("row_bcast:31 row_mask:0xc bank_mask:0xf") "s_nop 1"
+#define SR_ADD1(c) "v_add_f32_dpp %0, %0, %0 " c "\n\t"
+#define SR_ADD3(c) "v_add_f32_dpp %0, %0, %0 " c "\n\tv_add_f32_dpp %1, %1, %1 " c "\n\tv_add_f32_dpp %2, %2, %2 " c "\n\t"
+// (a maximum: lanes without a source keep their value)
+#define SR_MAX_STEPS(step, wait)                                                                              \
+  "s_nop 1\n\t" step("row_shr:1 row_mask:0xf bank_mask:0xf") wait step("row_shr:2 row_mask:0xf bank_mask:0xf") wait \
+      step("row_shr:4 row_mask:0xf bank_mask:0xf") wait step("row_shr:8 row_mask:0xf bank_mask:0xf") wait           \
+      step("row_bcast:15 row_mask:0xa bank_mask:0xf") wait step("row_bcast:31 row_mask:0xc bank_mask:0xf") "s_nop 1"
+#define SR_MAX1(c) "v_max_f32_dpp %0, %0, %0 " c "\n\t"
+#define SR_MAX2(c) "v_max_f32_dpp %0, %0, %0 " c "\n\tv_max_f32_dpp %1, %1, %1 " c "\n\t"
+__device__ __forceinline__ float lane63(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
+__device__ __forceinline__ float wave_total(float a) {
+  asm(SR_SUM_STEPS(SR_ADD1, "s_nop 1\n\t") : "+v"(a));
+  return lane63(a);
+}
+__device__ __forceinline__ void wave_total3(float& a, float& b, float& c) {
+  asm(SR_SUM_STEPS(SR_ADD3, "") : "+v"(a), "+v"(b), "+v"(c));
+  a = lane63(a);
+  b = lane63(b);
+  c = lane63(c);
+}
+__device__ __forceinline__ float wave_top(float a) {
+  asm(SR_MAX_STEPS(SR_MAX1, "s_nop 1\n\t") : "+v"(a));
+  return lane63(a);
+}
+__device__ __forceinline__ void wave_top2(float& a, float& b) {
+  asm(SR_MAX_STEPS(SR_MAX2, "s_nop 0\n\t") : "+v"(a), "+v"(b));
+  a = lane63(a);
+  b = lane63(b);
+}
+#undef SR_SUM_STEPS
+#undef SR_ADD1
+#undef SR_ADD3
+#undef SR_MAX_STEPS
+#undef SR_MAX1
+#undef SR_MAX2
+
+// The largest of a lane's entries (none of them NaN).
+template <int kE>
+__device__ __forceinline__ float lane_top(const float (&z)[kE]) {
+  float m = max_nn(z[0], z[1]);
+#pragma unroll
+  for (int e = 2; e < kE; e += 2) m = max3_nn(m, z[e], z[e + 1]);
+  return m;
 }
 
 // Pairwise sum of a lane's entries (a fixed tree).
@@ -481,7 +546,7 @@ __device__ __forceinline__ void store_rec(const __amdgpu_buffer_rsrc_t& rs, uint
 
 // Raw logits of one wave's entries, masked: entries outside the row and below
 // the row's top-k / top-p threshold become -inf.
-template <bool BF16>
+template <bool BF16, bool FILT>
 __device__ __forceinline__ void masked_logits(const Args& A, const TaskInfo& t, int wbase, const Loaded<BF16>& Lp,
                                               const Loaded<BF16>& Lq, float (&zp)[Vec<BF16>::E],
                                               float (&zq)[Vec<BF16>::E]) {
@@ -491,7 +556,7 @@ __device__ __forceinline__ void masked_logits(const Args& A, const TaskInfo& t, 
     mask_range<BF16>(zp, wbase, t.phi, A.V);
     mask_range<BF16>(zq, wbase, t.phi, A.V);
   }
-  if (A.thr) {  // workgroup-uniform
+  if constexpr (FILT) {
     mask_below(zp, t.thp);
     if (t.pair) mask_below(zq, t.thq);
   }
@@ -502,44 +567,73 @@ __device__ __forceinline__ void masked_logits(const Args& A, const TaskInfo& t, 
 __device__ __forceinline__ float shift_of(float m, float lg) { return m == kNegInf ? 0.f : ceilf(m * lg); }
 
 // The exponentials of one wave's entries under shifts rp, rq, their sums and
-// the KL numerator (groups of four entries summed as (a0 + a1) + (a2 + a3),
-// then a tree over the groups).
-template <int kE>
+// the KL numerator sum e_p (x_p - x_q) (groups of four entries summed as
+// (a0 + a1) + (a2 + a3), then a tree over the groups; the KL terms in four
+// running sums). INF: an entry may be -inf, whose KL term is 0 (p's) or +inf
+// (q's alone), with a multiply that makes 0 inf = 0; else one fma per entry,
+// and a NaN total tells that an entry was -inf after all.
+template <bool INF, int kE>
 __device__ __forceinline__ void wave_exps(const float (&zp)[kE], const float (&zq)[kE], float lg, float rp, float rq,
-                                          bool pair, float (&ep)[kE], float (&eq)[kE], double& sp, double& sq,
-                                          double& kl) {
-  float gp[kE / 4];
-  if (pair) {  // workgroup-uniform
-    float gq[kE / 4], gk[kE / 4];
+                                          float (&ep)[kE], float (&eq)[kE], float& sp, float& sq, float& kl) {
+  float gp[kE / 4], gq[kE / 4], gk[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int g = 0; g < kE / 4; ++g) {
-      float kt[4];
+  for (int g = 0; g < kE / 4; ++g) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = g * 4 + i;
-        const float xp = fmaf(zp[e], lg, -rp);
-        const float xq = fmaf(zq[e], lg, -rq);
-        ep[e] = exp2_hw(xp);
-        eq[e] = exp2_hw(xq);
-        kt[i] = sr_fmul_legacy(ep[e], xp - xq);  // 0 where p is -inf, +inf where only q is
-      }
-      gp[g] = (ep[g * 4] + ep[g * 4 + 1]) + (ep[g * 4 + 2] + ep[g * 4 + 3]);
-      gq[g] = (eq[g * 4] + eq[g * 4 + 1]) + (eq[g * 4 + 2] + eq[g * 4 + 3]);
-      gk[g] = (kt[0] + kt[1]) + (kt[2] + kt[3]);
+    for (int i = 0; i < 4; ++i) {
+      const int e = g * 4 + i;
+      const float xp = fmaf(zp[e], lg, -rp);
+      const float xq = fmaf(zq[e], lg, -rq);
+      ep[e] = exp2_hw(xp);
+      eq[e] = exp2_hw(xq);
+      if (INF) gk[i] += sr_fmul_legacy(ep[e], xp - xq);  // 0 where p is -inf, +inf where only q is
+      else gk[i] = g == 0 ? ep[e] * (xp - xq) : fmaf(ep[e], xp - xq, gk[i]);
     }
-    sq = (double)wave_sum(tree_sum(gq));
-    kl = (double)wave_sum(tree_sum(gk));
-  } else {  // a bonus row: p alone (eq is not read)
-#pragma unroll
-    for (int g = 0; g < kE / 4; ++g) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ep[g * 4 + i] = exp2_hw(fmaf(zp[g * 4 + i], lg, -rp));
-      gp[g] = (ep[g * 4] + ep[g * 4 + 1]) + (ep[g * 4 + 2] + ep[g * 4 + 3]);
-    }
-    sq = 0.0;
-    kl = 0.0;
+    gp[g] = (ep[g * 4] + ep[g * 4 + 1]) + (ep[g * 4 + 2] + ep[g * 4 + 3]);
+    gq[g] = (eq[g * 4] + eq[g * 4 + 1]) + (eq[g * 4 + 2] + eq[g * 4 + 3]);
   }
-  sp = (double)wave_sum(tree_sum(gp));
+  sp = tree_sum(gp);
+  sq = tree_sum(gq);
+  kl = (gk[0] + gk[1]) + (gk[2] + gk[3]);
+  wave_total3(sp, sq, kl);
+}
+// A bonus row: p alone (eq is not read).
+template <int kE>
+__device__ __forceinline__ float wave_exps_p(const float (&zp)[kE], float lg, float rp, float (&ep)[kE]) {
+  float gp[kE / 4];
+#pragma unroll
+  for (int g = 0; g < kE / 4; ++g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ep[g * 4 + i] = exp2_hw(fmaf(zp[g * 4 + i], lg, -rp));
+    gp[g] = (ep[g * 4] + ep[g * 4 + 1]) + (ep[g * 4 + 2] + ep[g * 4 + 3]);
+  }
+  return wave_total(tree_sum(gp));
+}
+
+// A wave's KL numerator again, from memory, when some logit is -inf (rare: the
+// first pass keeps no logits for it).
+template <bool BF16>
+__device__ __forceinline__ float wave_kl_again(const Args& A, const TaskInfo& t, int wbase, float rp, float rq) {
+  constexpr int N = Vec<BF16>::N, esz = Vec<BF16>::esz, kE = Vec<BF16>::E;
+  const int lane = threadIdx.x & 63;
+  const RowSpan s = row_span<BF16>(A, t.b, t.j, true);
+  float gk = 0.f;
+#pragma unroll 1
+  for (int i = 0; i < kE / N; ++i) {
+    const uint32_t off = (uint32_t)((wbase + (i * 64 + lane) * N) * esz);
+    const u32x4 up = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s.rp, off, 0, 0));
+    const u32x4 uq = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s.rq, off, 0, 0));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int h = 0; h < (BF16 ? 2 : 1); ++h) {
+        const float zp = !BF16 ? __uint_as_float(up[k]) : h ? bf16_hi(up[k]) : bf16_lo(up[k]);
+        const float zq = !BF16 ? __uint_as_float(uq[k]) : h ? bf16_hi(uq[k]) : bf16_lo(uq[k]);
+        const float xp = fmaf(zp, A.lg, -rp), xq = fmaf(zq, A.lg, -rq);
+        gk += sr_fmul_legacy(exp2_hw(xp), xp - xq);
+      }
+    }
+  }
+  return wave_total(gk);
 }
 
 // Sampling: each wave's maxima and shifts (its own: no exchange between the
@@ -548,7 +642,7 @@ __device__ __forceinline__ void wave_exps(const float (&zp)[kE], const float (&z
 // record, in the chunk's shifts (the largest of the waves'; the rescaling
 // factors are powers of two). Returns the wave's shifts, which its TV step
 // needs.
-template <bool BF16>
+template <bool BF16, bool FILT>
 __device__ __forceinline__ WaveShift first_pass(const Args& A, const TaskInfo& t, const Loaded<BF16>& Lp,
                                                 const Loaded<BF16>& Lq, float (&ep)[Vec<BF16>::E],
                                                 float (&eq)[Vec<BF16>::E], WaveSlots& sh,
@@ -557,28 +651,34 @@ __device__ __forceinline__ WaveShift first_pass(const Args& A, const TaskInfo& t
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wbase = t.c * Vec<BF16>::kChunk + w * Vec<BF16>::kWaveSpan;
   float zp[kE], zq[kE];
-  masked_logits<BF16>(A, t, wbase, Lp, Lq, zp, zq);
-  float mp = kNegInf, mq = kNegInf;
-#pragma unroll
-  for (int e = 0; e < kE; ++e) {
-    mp = fmaxf(mp, zp[e]);
-    mq = fmaxf(mq, zq[e]);
+  masked_logits<BF16, FILT>(A, t, wbase, Lp, Lq, zp, zq);
+  float mp = lane_top(zp), mq = kNegInf, sp, sq = 0.f, kl = 0.f, rp, rq = 0.f;
+  if (t.pair) {  // workgroup-uniform
+    mq = lane_top(zq);
+    wave_top2(mp, mq);
+    rp = shift_of(mp, A.lg);
+    rq = shift_of(mq, A.lg);
+    store_xlogit<BF16>(A, t, wbase, zp, zq, rp, rq);
+    if (!FILT && t.full) {
+      wave_exps<false>(zp, zq, A.lg, rp, rq, ep, eq, sp, sq, kl);
+      if (kl != kl) kl = wave_kl_again<BF16>(A, t, wbase, rp, rq);
+    } else {
+      wave_exps<true>(zp, zq, A.lg, rp, rq, ep, eq, sp, sq, kl);
+    }
+  } else {
+    mp = wave_top(mp);
+    rp = shift_of(mp, A.lg);
+    sp = wave_exps_p(zp, A.lg, rp, ep);
   }
-  mp = wave_max(mp);
-  mq = t.pair ? wave_max(mq) : kNegInf;
-  const float rp = shift_of(mp, A.lg), rq = shift_of(mq, A.lg);
-  if (t.pair) store_xlogit<BF16>(A, t, wbase, zp, zq, rp, rq);
-  double sp, sq, kl;
-  wave_exps(zp, zq, A.lg, rp, rq, t.pair, ep, eq, sp, sq, kl);
   WaveShift ws;
   ws.rp = mp == kNegInf ? kNegInf : rp;
   ws.rq = mq == kNegInf ? kNegInf : rq;
   if (lane == 0) {
     sh.m[0][w] = ws.rp;
     sh.m[1][w] = ws.rq;
-    sh.s[0][w] = sp;
-    sh.s[1][w] = sq;
-    sh.s[2][w] = kl;
+    sh.s[0][w] = (double)sp;
+    sh.s[1][w] = (double)sq;
+    sh.s[2][w] = (double)kl;
   }
   __syncthreads();
   if (w == builder && lane == 0) {
@@ -700,22 +800,25 @@ __device__ __forceinline__ void to_sweep(const Args& A, int b, int j) {
 // Row merges (one wave; the same code wherever a row is merged, so every
 // merge of a row gives the same bits)
 
-// A row's chunk records, lane-wise: chunk lane * kSlots + i in slot i.
+// A row's chunk records, lane-wise: chunk lane * NS + i in slot i.
+template <int NS>
 struct RowRecs {
-  float rp[kSlots], rq[kSlots];
-  double sp[kSlots], sq[kSlots], kl[kSlots];
+  float rp[NS], rq[NS];
+  double sp[NS], sq[NS], kl[NS];
 };
 
 // A row's record words as loaded (device-coherent loads), lane-wise.
+template <int NS>
 struct RecWords {
-  u32x4 w[kSlots][2];
+  u32x4 w[NS][2];
 };
 
-__device__ __forceinline__ void issue_recs(const Args& A, const __amdgpu_buffer_rsrc_t& rs, int row, RecWords& W) {
+template <int NS>
+__device__ __forceinline__ void issue_recs(const Args& A, const __amdgpu_buffer_rsrc_t& rs, int row, RecWords<NS>& W) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
-    const int c = lane * kSlots + i;
+  for (int i = 0; i < NS; ++i) {
+    const int c = lane * NS + i;
     const uint32_t off = rec_off(row, A.nc, c < A.nc ? c : 0);
     W.w[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kDeviceCoherent);
     W.w[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, kDeviceCoherent);
@@ -723,12 +826,13 @@ __device__ __forceinline__ void issue_recs(const Args& A, const __amdgpu_buffer_
 }
 
 // The records from their words; true (wave-uniform) when all are present.
-__device__ __forceinline__ bool decode_recs(const Args& A, const RecWords& W, RowRecs& R) {
+template <int NS>
+__device__ __forceinline__ bool decode_recs(const Args& A, const RecWords<NS>& W, RowRecs<NS>& R) {
   const int lane = threadIdx.x & 63;
   bool ok = true;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
-    const int c = lane * kSlots + i;
+  for (int i = 0; i < NS; ++i) {
+    const int c = lane * NS + i;
     const bool in = c < A.nc;
     const u32x4 w0 = W.w[i][0], w1 = W.w[i][1];
     ok = ok && (!in || rec_present(w0, w1));
@@ -743,8 +847,9 @@ __device__ __forceinline__ bool decode_recs(const Args& A, const RecWords& W, Ro
 }
 
 // Loads the records; true (wave-uniform) when all are present.
-__device__ __forceinline__ bool load_recs(const Args& A, const __amdgpu_buffer_rsrc_t& rs, int row, RowRecs& R) {
-  RecWords W;
+template <int NS>
+__device__ __forceinline__ bool load_recs(const Args& A, const __amdgpu_buffer_rsrc_t& rs, int row, RowRecs<NS>& R) {
+  RecWords<NS> W;
   issue_recs(A, rs, row, W);
   return decode_recs(A, W, R);
 }
@@ -761,16 +866,17 @@ __device__ __forceinline__ double pow2(float r, float rM) {
   return r == kNegInf ? 0.0 : ldexp(1.0, (int)(r - rM));
 }
 
-__device__ __forceinline__ Norm merge_norm(const float (&r)[kSlots], const double (&s)[kSlots]) {
+template <int NS>
+__device__ __forceinline__ Norm merge_norm(const float (&r)[NS], const double (&s)[NS]) {
   float m = kNegInf;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) m = fmaxf(m, r[i]);
+  for (int i = 0; i < NS; ++i) m = fmaxf(m, r[i]);
   Norm n;
   n.rM = wave_max(m);
   double acc = 0.0;
   if (n.rM != kNegInf) {
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i) acc += s[i] * pow2(r[i], n.rM);
+    for (int i = 0; i < NS; ++i) acc += s[i] * pow2(r[i], n.rM);
   }
   n.S = wave_sum_d(acc);
   return n;
@@ -781,55 +887,49 @@ __device__ __forceinline__ double factor(float r, const Norm& n) {
   return (r == kNegInf || !(n.S > 0.0)) ? 0.0 : pow2(r, n.rM) / n.S;
 }
 
-// The TV sum of a chunk with factors fp, fq is scale * sum |fma(e_p, rho_p,
-// -e_q rho_q)|: the larger factor is scale, and of the two ratios rho = f/scale
-// the larger side's is exactly 1 (so rows with equal factors subtract
-// exactly, and the product on that side is exact).
-struct TvPar {
-  double scale;
-  float rho_p, rho_q;
-};
 // 1/s (s > 0) from the hardware estimate and two Newton steps.
 __device__ __forceinline__ double recip(double s) {
   double r = __builtin_amdgcn_rcp(s);
   r = fma(r, fma(-s, r, 1.0), r);
   return fma(r, fma(-s, r, 1.0), r);
 }
-// The factors of a wave with shifts ws against the row normalisers, without a
-// division: f = 2^(r_w - r_max)/S, and the smaller side's ratio is
-// 2^(k) S_big/S_small with k the difference of the shift offsets.
+// A wave's share of a chunk's TV sum in units of the row's 1/S_q: its entries
+// are p = e_p f_p, q = e_q f_q with f_p = 2^a/S_p, f_q = 2^b/S_q (a, b: its shifts
+// against the row's), so sum |p - q| = 2^e/S_q sum |e_p c - e_q| with c = f_p/f_q
+// = 2^(a-b) S_q/S_p and e = b: one fma and one add per entry, the factors a
+// reciprocal and two exponents per wave. (With both sides scaled by ratios of
+// at most 1 an entry took three instructions and the factors about fifty per
+// wave.) Rows with equal factors have c = 1 and subtract exactly. c is held
+// to 2^60 times S_q/S_p: beyond, e takes the rest, and the q side is then too
+// large by that power of two, below 2^-50 of the p side.
+struct TvPar {
+  float c;
+  int e;
+};
 __device__ __forceinline__ TvPar tv_par(const WaveShift& ws, const Norm& np, const Norm& nq) {
-  const bool hp = ws.rp != kNegInf && np.S > 0.0, hq = ws.rq != kNegInf && nq.S > 0.0;
-  const double ip = recip(hp ? np.S : 1.0), iq = recip(hq ? nq.S : 1.0);
-  const int a = hp ? (int)(ws.rp - np.rM) : 0, b = hq ? (int)(ws.rq - nq.rM) : 0;
-  const double fp = hp ? ldexp(ip, a) : 0.0, fq = hq ? ldexp(iq, b) : 0.0;
-  const bool both = hp && hq;
-  const float rq = both ? (float)ldexp(np.S * iq, b - a) : 0.f;  // f_q/f_p
-  const float rp = both ? (float)ldexp(nq.S * ip, a - b) : 0.f;  // f_p/f_q
-  const bool pbig = fp >= fq;
+  // (a side without entries in the wave: its exponentials are 0, any shift will do)
+  const int a = ws.rp != kNegInf ? (int)(ws.rp - np.rM) : 0, b = ws.rq != kNegInf ? (int)(ws.rq - nq.rM) : 0;
+  const int k = max(a - b, -1000), over = max(k - 60, 0);
   TvPar t;
-  t.scale = pbig ? fp : fq;
-  t.rho_p = pbig ? (hp ? 1.f : 0.f) : rp;
-  t.rho_q = pbig ? rq : 1.f;
+  t.c = ldexpf((float)(nq.S * recip(np.S)), k - over);
+  t.e = b + over;
   return t;
 }
-// One entry's scaled difference e_p rho_p - e_q rho_q.
-__device__ __forceinline__ float tv_diff(float ep, float eq, float rho_p, float rho_q) {
-  return fmaf(ep, rho_p, -(eq * rho_q));
-}
+// One entry's difference in those units.
+__device__ __forceinline__ float tv_diff(float ep, float eq, float c) { return fmaf(ep, c, -eq); }
 
-// One wave's part of a chunk's TV sum.
+// One wave's part of a chunk's TV sum (in every lane).
 template <int kE>
-__device__ __forceinline__ double tv_wave(const float (&ep)[kE], const float (&eq)[kE], float rho_p, float rho_q) {
+__device__ __forceinline__ float tv_wave(const float (&ep)[kE], const float (&eq)[kE], float c) {
   float g[kE / 4];
 #pragma unroll
   for (int k = 0; k < kE / 4; ++k) {
     float d[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) d[i] = fabsf(tv_diff(ep[k * 4 + i], eq[k * 4 + i], rho_p, rho_q));
+    for (int i = 0; i < 4; ++i) d[i] = fabsf(tv_diff(ep[k * 4 + i], eq[k * 4 + i], c));
     g[k] = (d[0] + d[1]) + (d[2] + d[3]);
   }
-  return (double)wave_sum(tree_sum(g));
+  return wave_total(tree_sum(g));
 }
 // A chunk's TV sum from its waves' parts, in a fixed order.
 __device__ __forceinline__ double tv_chunk(const double (&part)[kWaves]) {
@@ -843,10 +943,11 @@ __device__ __forceinline__ float lane_float(float x, int src) {
 // The polling wave: the row's records from the words of a first attempt (W,
 // issued earlier), else re-loaded until all are present (for a bounded
 // time); merge them and leave the row's normalisers in LDS.
+template <int NS>
 __device__ __forceinline__ void poll_row(const Args& A, const __amdgpu_buffer_rsrc_t& rs, const TaskInfo& t,
-                                         const RecWords& W, TaskShared& sh) {
+                                         const RecWords<NS>& W, TaskShared& sh) {
   const int lane = threadIdx.x & 63;
-  RowRecs R;
+  RowRecs<NS> R;
   bool ok = decode_recs(A, W, R);
   if (!ok) {
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
@@ -869,13 +970,12 @@ __device__ __forceinline__ void poll_row(const Args& A, const __amdgpu_buffer_rs
   if (lane == 0) sh.ok = ok ? 1 : 0;
 }
 
-// A wave's share of a chunk's TV sum, scaled: scale * sum |e_p rho_p - e_q rho_q|
-// with the wave's own factors against the row normalisers.
+// A wave's share of a chunk's TV sum in units of 1/S_q.
 template <int kE>
 __device__ __forceinline__ double tv_wave_scaled(const float (&ep)[kE], const float (&eq)[kE], const WaveShift& ws,
                                                  const Norm& np, const Norm& nq) {
   const TvPar par = tv_par(ws, np, nq);
-  return par.scale * tv_wave(ep, eq, par.rho_p, par.rho_q);
+  return ldexp((double)tv_wave(ep, eq, par.c), par.e);
 }
 
 // ---------------------------------------------------------------------------
@@ -1008,17 +1108,17 @@ struct DrawPlan {
   int c, resid;
 };
 
-template <bool BF16>
-__device__ DrawPlan draw_plan(const Args& A, int b, int k, int gam, float u, const RowRecs& R, const Norm& np,
-                              const Norm& nq, const double (&tva)[kSlots]) {
+template <bool BF16, int NS>
+__device__ DrawPlan draw_plan(const Args& A, int b, int k, int gam, float u, const RowRecs<NS>& R, const Norm& np,
+                              const Norm& nq, const double (&tva)[NS]) {
   const int lane = threadIdx.x & 63;
   const int row = b * (A.gmax + 1) + k;
   const bool pair = k < gam;
-  double mres[kSlots], mp[kSlots];
+  double mres[NS], mp[NS];
   double my_res = 0.0;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
-    const int c = lane * kSlots + i;
+  for (int i = 0; i < NS; ++i) {
+    const int c = lane * NS + i;
     const double fp = factor(R.rp[i], np);
     mp[i] = fp * R.sp[i];
     mres[i] = 0.0;
@@ -1029,13 +1129,13 @@ __device__ DrawPlan draw_plan(const Args& A, int b, int k, int gam, float u, con
     my_res += mres[i];
   }
   const bool resid = pair && wave_sum_d(my_res) > 0.0;
-  double m[kSlots], my = 0.0;
+  double m[NS], my = 0.0;
   int my_last = -1;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
+  for (int i = 0; i < NS; ++i) {
     m[i] = resid ? mres[i] : mp[i];
     my += m[i];
-    if (m[i] > 0.0) my_last = lane * kSlots + i;
+    if (m[i] > 0.0) my_last = lane * NS + i;
   }
   const double incl = wave_incl_scan_d(my);
   const double W = lane_value(incl, 63);
@@ -1050,9 +1150,9 @@ __device__ DrawPlan draw_plan(const Args& A, int b, int k, int gam, float u, con
     int found = -1;
     double fpre = 0.0;
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i) {
+    for (int i = 0; i < NS; ++i) {
       if (found < 0 && m[i] > 0.0 && run + m[i] > target) {
-        found = lane * kSlots + i;
+        found = lane * NS + i;
         fpre = run;
       }
       run += m[i];
@@ -1063,8 +1163,8 @@ __device__ DrawPlan draw_plan(const Args& A, int b, int k, int gam, float u, con
     c = max(wave_max_i(my_last), 0);
     double before = 0.0;
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i)
-      if (lane * kSlots + i < c) before += m[i];
+    for (int i = 0; i < NS; ++i)
+      if (lane * NS + i < c) before += m[i];
     pre = wave_sum_d(before);
   }
   const double rem = target - pre;
@@ -1113,13 +1213,13 @@ __device__ __forceinline__ double draw_weights(const Args& A, int b, int k, cons
     mp = fmaxf(mp, zp[e]);
     mq = fmaxf(mq, zq[e]);
   }
-  mp = wave_max(mp);
-  mq = d.resid ? wave_max(mq) : kNegInf;
+  wave_top2(mp, mq);
+  if (!d.resid) mq = kNegInf;
   const float rp = shift_of(mp, A.lg), rq = shift_of(mq, A.lg);
   const WaveShift ws{mp == kNegInf ? kNegInf : rp, mq == kNegInf ? kNegInf : rq};
   const Norm np{d.rM_p, d.S_p}, nq{d.rM_q, d.S_q};
   const double fp = factor(ws.rp, np);
-  const TvPar par = d.resid ? tv_par(ws, np, nq) : TvPar{fp, 1.f, 0.f};
+  const TvPar par = d.resid ? tv_par(ws, np, nq) : TvPar{1.f, 0};
   mine = -1;
 #pragma unroll
   for (int e = 0; e < kE; ++e) {
@@ -1128,14 +1228,14 @@ __device__ __forceinline__ double draw_weights(const Args& A, int b, int k, cons
     float wv;
     if (d.resid) {
       const float eq = exp2_hw(fmaf(zq[e], A.lg, -rq));
-      wv = fmaxf(tv_diff(ep, eq, par.rho_p, par.rho_q), 0.f);
+      wv = fmaxf(tv_diff(ep, eq, par.c), 0.f);
     } else {
       wv = ep;
     }
     wt[e] = wv;
     if (wv > 0.f) mine = i;
   }
-  return d.resid ? par.scale : fp;
+  return d.resid ? ldexp(recip(nq.S), par.e) : fp;
 }
 
 // Shared state of the scan.
@@ -1204,9 +1304,9 @@ __device__ int draw_scan(const Args& A, int b, int k, const DrawPlan& d, DrawSha
 // Recompute the sums of the chunks whose owners gave up waiting, from memory,
 // with the owners' arithmetic and layout (one wave takes the four waves'
 // entries in turn and combines their parts in the same order: same bits).
-template <bool BF16>
-__device__ void redo_skipped(const Args& A, int b, int j, const RowRecs& R, const Norm& np, const Norm& nq,
-                             double (&tva)[kSlots]) {
+template <bool BF16, int NS>
+__device__ void redo_skipped(const Args& A, int b, int j, const RowRecs<NS>& R, const Norm& np, const Norm& nq,
+                             double (&tva)[NS]) {
   constexpr int N = Vec<BF16>::N, esz = Vec<BF16>::esz, kE = Vec<BF16>::E;
   constexpr int kChunk = Vec<BF16>::kChunk, kWaveSpan = Vec<BF16>::kWaveSpan;
   const int lane = threadIdx.x & 63;
@@ -1215,8 +1315,8 @@ __device__ void redo_skipped(const Args& A, int b, int j, const RowRecs& R, cons
   for (;;) {
     int cl = -1;
 #pragma unroll
-    for (int i = kSlots - 1; i >= 0; --i)
-      if (tva[i] == kSkipped) cl = lane * kSlots + i;
+    for (int i = NS - 1; i >= 0; --i)
+      if (tva[i] == kSkipped) cl = lane * NS + i;
     const unsigned long long pend = __ballot(cl >= 0);
     if (!pend) break;
     const int src = __ffsll((long long)pend) - 1;
@@ -1241,7 +1341,8 @@ __device__ void redo_skipped(const Args& A, int b, int j, const RowRecs& R, cons
         lq.v[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s.rq, off, 0, 0));
       }
       float zp[kE], zq[kE], ep[kE], eq[kE];
-      masked_logits<BF16>(A, t, wbase, lp, lq, zp, zq);
+      if (A.thr) masked_logits<BF16, true>(A, t, wbase, lp, lq, zp, zq);
+      else masked_logits<BF16, false>(A, t, wbase, lp, lq, zp, zq);
       // the owner wave's shifts: its maxima over these entries
       float mp = kNegInf, mq = kNegInf;
 #pragma unroll
@@ -1263,8 +1364,8 @@ __device__ void redo_skipped(const Args& A, int b, int j, const RowRecs& R, cons
     const double sum = tv_chunk(part);  // the owners' parts, combined as the finaliser combines them
     if (lane == src) {
 #pragma unroll
-      for (int i = 0; i < kSlots; ++i)
-        if (lane * kSlots + i == c) tva[i] = sum;
+      for (int i = 0; i < NS; ++i)
+        if (lane * NS + i == c) tva[i] = sum;
     }
   }
 }
@@ -1273,22 +1374,22 @@ __device__ void redo_skipped(const Args& A, int b, int j, const RowRecs& R, cons
 // the draw the sequence would make if it stopped at row j, from u_res[j]; the
 // finisher uses one of those once the accept chain is known. Every load the
 // row needs is issued first, then consumed.
-template <bool BF16, bool GREEDY>
+template <bool BF16, bool GREEDY, int NS>
 __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amdgpu_buffer_rsrc_t& rs_recs,
                                DrawPlan& plan) {
   const int lane = threadIdx.x & 63;
   const int row = b * (A.gmax + 1) + j;
   const bool pair = j < gam;
-  RecWords W;
+  RecWords<NS> W;
   issue_recs(A, rs_recs, row, W);  // all present: the sweep launch has completed
-  double part[kSlots][kWaves];
+  double part[NS][kWaves];
   float xs[4] = {0.f, 0.f, 0.f, 0.f};
   float u = 0.f;
   if (!GREEDY) {
     if (pair) {
 #pragma unroll
-      for (int i = 0; i < kSlots; ++i) {
-        const int c = lane * kSlots + i;
+      for (int i = 0; i < NS; ++i) {
+        const int c = lane * NS + i;
         const double* tp = A.tva + ((size_t)row * A.nc + (c < A.nc ? c : 0)) * kWaves;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) part[i][w] = tp[w];
@@ -1299,7 +1400,7 @@ __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amd
     u = A.u_res[row];
   }
   const int x = pair ? A.drafts[(size_t)b * A.gmax + j] : -1;
-  RowRecs R;
+  RowRecs<NS> R;
   decode_recs(A, W, R);
   RowOut o;
   o.pad = 0;
@@ -1309,7 +1410,7 @@ __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amd
   if constexpr (GREEDY) {
     float mp = kNegInf, mq = kNegInf;
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i) {
+    for (int i = 0; i < NS; ++i) {
       mp = fmaxf(mp, R.rp[i]);
       mq = fmaxf(mq, R.rq[i]);
     }
@@ -1317,8 +1418,8 @@ __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amd
     mq = wave_max(mq);
     int ap = INT_MAX, aq = INT_MAX;
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i) {
-      const bool in = lane * kSlots + i < A.nc;
+    for (int i = 0; i < NS; ++i) {
+      const bool in = lane * NS + i < A.nc;
       if (in && R.rp[i] == mp) ap = min(ap, (int)R.sp[i]);
       if (in && R.rq[i] == mq) aq = min(aq, (int)R.sq[i]);
     }
@@ -1334,28 +1435,32 @@ __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amd
   } else {
     const Norm np = merge_norm(R.rp, R.sp);
     Norm nq = Norm{kNegInf, 0.0};
-    double tva[kSlots];
+    double tva[NS];
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i) {
+    for (int i = 0; i < NS; ++i) {
       // a chunk's TV sum: its four waves' parts in a fixed order; kSkipped if
       // any part was left to the finaliser; 0 past the row
       bool skipped = false;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) skipped = skipped || part[i][w] == kSkipped;
-      tva[i] = lane * kSlots + i >= A.nc ? 0.0 : skipped ? kSkipped : tv_chunk(part[i]);
+      tva[i] = lane * NS + i >= A.nc ? 0.0 : skipped ? kSkipped : tv_chunk(part[i]);
     }
+
     o.a = 0.0;
     o.p_tok = o.q_tok = o.kl = o.tv = nan;
     if (pair) {
       nq = merge_norm(R.rq, R.sq);
-      redo_skipped<BF16>(A, b, j, R, np, nq, tva);
+      redo_skipped<BF16, NS>(A, b, j, R, np, nq, tva);
+      const double iq = recip(nq.S);  // the unit of the TV parts
+#pragma unroll
+      for (int i = 0; i < NS; ++i) tva[i] *= iq;
       // TV = 1/2 sum_c tva_c (the waves' parts come scaled);
       // KL = sum_c f_c (ln2 kl_c + ln2 s_c d_c) - ln(S_p / S_q) sum_c f_c s_c with
       // d_c = (r_c - r_max) - (r'_c - r'_max) (integers): the log-ratio of an
       // entry is ln2 (x_p - x_q) + ln2 d_c - ln(S_p / S_q)
       double tvs = 0.0, klt = 0.0, mass = 0.0;
 #pragma unroll
-      for (int i = 0; i < kSlots; ++i) {
+      for (int i = 0; i < NS; ++i) {
         const double fp = factor(R.rp[i], np);
         tvs += tva[i];
         if (fp > 0.0) {
@@ -1379,7 +1484,7 @@ __device__ RowOut finalize_row(const Args& A, int b, int j, int gam, const __amd
       o.kl = (float)kl;
       o.tv = (float)tv;
     }
-    plan = draw_plan<BF16>(A, b, j, gam, u, R, np, nq, tva);
+    plan = draw_plan<BF16, NS>(A, b, j, gam, u, R, np, nq, tva);
   }
   return o;
 }
@@ -1712,7 +1817,7 @@ __device__ void finish_sequence(const Args& A, int b, int gam, const RowOut* row
 // return during this task's first pass); every wave issues the next task's
 // loads; the first pass of task k; then the previous task's TV sum, with its
 // exponentials kept in registers. Returns whether a next task exists.
-template <bool BF16, bool GREEDY>
+template <bool BF16, bool GREEDY, bool FILT, int NS>
 __device__ __forceinline__ bool sweep_step(const Args& A, const int* s_rows, long n_tasks, int n_my, int k,
                                            TaskTable& tab, TaskShared& sh, const __amdgpu_buffer_rsrc_t& rs_recs,
                                            const TaskInfo& cur, const Loaded<BF16>& lp, const Loaded<BF16>& lq,
@@ -1725,17 +1830,17 @@ __device__ __forceinline__ bool sweep_step(const Args& A, const int* s_rows, lon
   // The poll and the merge of the records go to wave k mod 4, so that every
   // SIMD gets its share of that work.
   const bool poller = w == (k & (kWaves - 1));
-  RecWords W;
+  RecWords<NS> W;
   if (tv && poller) issue_recs(A, rs_recs, prev.row, W);
   // The table is refilled when the next task starts a new window (every read
   // of the old window came before the previous task's barriers); past the
   // end the prefetch reads through an empty resource.
   const bool more = k + 1 < n_my;
-  if (more && (k + 1) % kTab == 0) fill_tasks(A, s_rows, n_tasks, k + 1, tab);
-  nxt = decode_task<BF16>(A, tab, more ? k + 1 : k);
+  if (more && (k + 1) % kTab == 0) fill_tasks<FILT>(A, s_rows, n_tasks, k + 1, tab);
+  nxt = decode_task<BF16, FILT>(A, tab, more ? k + 1 : k);
   issue_loads<BF16>(A, nxt, np_, nq_, more);
   if constexpr (GREEDY) argmax_pass<BF16>(A, cur, lp, lq, sh.x[k & 1], rs_recs);
-  else ws = first_pass<BF16>(A, cur, lp, lq, ep, eq, sh.x[k & 1], rs_recs, (k + 2) & (kWaves - 1));
+  else ws = first_pass<BF16, FILT>(A, cur, lp, lq, ep, eq, sh.x[k & 1], rs_recs, (k + 2) & (kWaves - 1));
   if (tv) {
     if (poller) poll_row(A, rs_recs, prev, W, sh);
     __syncthreads();
@@ -1748,14 +1853,14 @@ __device__ __forceinline__ bool sweep_step(const Args& A, const int* s_rows, lon
 }
 
 // The TV sum of the last task (nothing left to overlap its poll with).
-template <bool BF16>
+template <bool BF16, int NS>
 __device__ __forceinline__ void sweep_last_tv(const Args& A, TaskShared& sh, const __amdgpu_buffer_rsrc_t& rs_recs,
                                               const TaskInfo& prev, const float (&pp)[Vec<BF16>::E],
                                               const float (&pq)[Vec<BF16>::E], const WaveShift& pws) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (!prev.pair) return;
   if (w == 0) {
-    RecWords W;
+    RecWords<NS> W;
     issue_recs(A, rs_recs, prev.row, W);
     poll_row(A, rs_recs, prev, W, sh);
   }
@@ -1770,35 +1875,35 @@ __device__ __forceinline__ void sweep_last_tv(const Args& A, TaskShared& sh, con
 // loading one task ahead and finishing each pair task's TV sum during the next
 // task. The loop body is unrolled twice so that the two sets of loaded vectors
 // and of exponentials swap roles without copies.
-template <bool BF16, bool GREEDY>
-__global__ void __launch_bounds__(kThreads, 2) accept_kernel(Args A) {
+template <bool BF16, bool GREEDY, bool FILT, int NS>
+__global__ void __launch_bounds__(kThreads, NS == 1 ? 3 : 2) accept_kernel(Args A) {
   constexpr int E = Vec<BF16>::E;
   extern __shared__ int s_rows[];  // [B] inclusive prefix of live rows
   __shared__ TaskShared sh;
   __shared__ TaskTable tab;
-  if (!GREEDY && A.smask && *A.swany == 0u) return;  // every row is listed
-  build_row_table(A.gamma, A.smask, A.gmax, A.B, s_rows);
+  if (FILT && A.smask && *A.swany == 0u) return;  // every row is listed
+  build_row_table(A.gamma, FILT ? A.smask : nullptr, A.gmax, A.B, s_rows);
   const long n_tasks = (long)s_rows[A.B - 1] * A.nc;
   if (blockIdx.x >= n_tasks) return;
   const int n_my = (int)((n_tasks - blockIdx.x + gridDim.x - 1) / gridDim.x);  // this workgroup's tasks
   const __amdgpu_buffer_rsrc_t rs_recs = make_rsrc(A.recs, (size_t)A.B * (A.gmax + 1) * A.nc * kRecBytes);
-  fill_tasks(A, s_rows, n_tasks, 0, tab);
-  TaskInfo ta = decode_task<BF16>(A, tab, 0), tb = ta;
+  fill_tasks<FILT>(A, s_rows, n_tasks, 0, tab);
+  TaskInfo ta = decode_task<BF16, FILT>(A, tab, 0), tb = ta;
   Loaded<BF16> pa, qa, pb, qb;
   issue_loads<BF16>(A, ta, pa, qa);
   float epa[E], eqa[E], epb[E], eqb[E];
   WaveShift wsa{kNegInf, kNegInf}, wsb{kNegInf, kNegInf};
   bool has_prev = false;
   for (int k = 0;; k += 2) {
-    if (!sweep_step<BF16, GREEDY>(A, s_rows, n_tasks, n_my, k, tab, sh, rs_recs, ta, pa, qa, epa, eqa, wsa, tb,
+    if (!sweep_step<BF16, GREEDY, FILT, NS>(A, s_rows, n_tasks, n_my, k, tab, sh, rs_recs, ta, pa, qa, epa, eqa, wsa, tb,
                                   has_prev, epb, eqb, wsb, tb, pb, qb)) {
-      if (!GREEDY) sweep_last_tv<BF16>(A, sh, rs_recs, ta, epa, eqa, wsa);
+      if (!GREEDY) sweep_last_tv<BF16, NS>(A, sh, rs_recs, ta, epa, eqa, wsa);
       break;
     }
     has_prev = true;
-    if (!sweep_step<BF16, GREEDY>(A, s_rows, n_tasks, n_my, k + 1, tab, sh, rs_recs, tb, pb, qb, epb, eqb, wsb, ta,
+    if (!sweep_step<BF16, GREEDY, FILT, NS>(A, s_rows, n_tasks, n_my, k + 1, tab, sh, rs_recs, tb, pb, qb, epb, eqb, wsb, ta,
                                   true, epa, eqa, wsa, ta, pa, qa)) {
-      if (!GREEDY) sweep_last_tv<BF16>(A, sh, rs_recs, tb, epb, eqb, wsb);
+      if (!GREEDY) sweep_last_tv<BF16, NS>(A, sh, rs_recs, tb, epb, eqb, wsb);
       break;
     }
   }
@@ -1811,7 +1916,7 @@ __global__ void __launch_bounds__(kThreads, 2) accept_kernel(Args A) {
 // outside [0, gamma_max] gets the invalid outputs. LIST: rows may be listed
 // (a kernel of its own: the lists' registers stay out of the plain one).
 
-template <bool BF16, bool GREEDY, bool LIST>
+template <bool BF16, bool GREEDY, bool LIST, int NS>
 __global__ void __launch_bounds__(64 * kFinWaves) accept_finish_kernel(Args A) {
   __shared__ RowOut s_out[kMaxRows];
   __shared__ DrawPlan s_plan[kMaxRows];
@@ -1839,7 +1944,7 @@ __global__ void __launch_bounds__(64 * kFinWaves) accept_finish_kernel(Args A) {
       }
     }
     DrawPlan plan;
-    const RowOut o = finalize_row<BF16, GREEDY>(A, b, j, gam, rs_recs, plan);
+    const RowOut o = finalize_row<BF16, GREEDY, NS>(A, b, j, gam, rs_recs, plan);
     if (lane == 0) {
       s_out[j] = o;
       if (!GREEDY) s_plan[j] = plan;
@@ -1897,6 +2002,25 @@ int resident_per_cu(const void* fn, size_t lds) {
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kThreads, lds) != hipSuccess || per_cu < 1)
     per_cu = 1;
   return per_cu;
+}
+
+typedef void (*Kernel)(Args);
+template <bool BF16, int NS>
+Kernel sweep_kernel(bool greedy, bool filt) {
+  return greedy ? accept_kernel<BF16, true, false, NS> : filt ? accept_kernel<BF16, false, true, NS> : accept_kernel<BF16, false, false, NS>;
+}
+template <bool BF16>
+Kernel sweep_kernel(bool greedy, bool filt, bool one) {
+  return one ? sweep_kernel<BF16, 1>(greedy, filt) : sweep_kernel<BF16, kMaxSlots>(greedy, filt);
+}
+template <bool BF16, int NS>
+Kernel finish_kernel(bool greedy, bool list) {
+  return greedy ? accept_finish_kernel<BF16, true, false, NS>
+         : list ? accept_finish_kernel<BF16, false, true, NS> : accept_finish_kernel<BF16, false, false, NS>;
+}
+template <bool BF16>
+Kernel finish_kernel(bool greedy, bool list, bool one) {
+  return one ? finish_kernel<BF16, 1>(greedy, list) : finish_kernel<BF16, kMaxSlots>(greedy, list);
 }
 
 // The persistent grid of a launch: what fits on the device at once, a
@@ -2035,9 +2159,10 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     A.rb_lcap = rollback ? rollback->L_cap : 0;
     A.n_before = b0;
     const long max_tasks = (long)Bl * G1 * nc;
-    const void* fn = dtype == SR_BF16 ? (greedy ? (const void*)accept_kernel<true, true> : (const void*)accept_kernel<true, false>)
-                                      : (greedy ? (const void*)accept_kernel<false, true> : (const void*)accept_kernel<false, false>);
-    const int n_wg = persistent_grid(fn, max_tasks, Bl, nc);
+    const bool one = nc <= 64;  // chunk records per lane of a row merge
+    const Kernel sweep = dtype == SR_BF16 ? sweep_kernel<true>(greedy, filt, one) : sweep_kernel<false>(greedy, filt, one);
+    const Kernel finish = dtype == SR_BF16 ? finish_kernel<true>(greedy, list, one) : finish_kernel<false>(greedy, list, one);
+    const int n_wg = persistent_grid((const void*)sweep, max_tasks, Bl, nc);
     if (n_wg == 0) return SR_ELAUNCH;
     const size_t lds = Bl * sizeof(int);  // the row table
     if (filt) {  // the rows' top-k / top-p thresholds first
@@ -2055,25 +2180,9 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
       }
       if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
     }
-    const dim3 grid((unsigned)n_wg), block(kThreads);
-    if (dtype == SR_BF16) {
-      if (greedy) hipLaunchKernelGGL((accept_kernel<true, true>), grid, block, lds, stream, A);
-      else hipLaunchKernelGGL((accept_kernel<true, false>), grid, block, lds, stream, A);
-    } else {
-      if (greedy) hipLaunchKernelGGL((accept_kernel<false, true>), grid, block, lds, stream, A);
-      else hipLaunchKernelGGL((accept_kernel<false, false>), grid, block, lds, stream, A);
-    }
+    hipLaunchKernelGGL(sweep, dim3((unsigned)n_wg), dim3(kThreads), lds, stream, A);
     if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
-    const dim3 grid_s((unsigned)Bl), block_s(64 * kFinWaves);
-    if (dtype == SR_BF16) {
-      if (greedy) hipLaunchKernelGGL((accept_finish_kernel<true, true, false>), grid_s, block_s, 0, stream, A);
-      else if (list) hipLaunchKernelGGL((accept_finish_kernel<true, false, true>), grid_s, block_s, 0, stream, A);
-      else hipLaunchKernelGGL((accept_finish_kernel<true, false, false>), grid_s, block_s, 0, stream, A);
-    } else {
-      if (greedy) hipLaunchKernelGGL((accept_finish_kernel<false, true, false>), grid_s, block_s, 0, stream, A);
-      else if (list) hipLaunchKernelGGL((accept_finish_kernel<false, false, true>), grid_s, block_s, 0, stream, A);
-      else hipLaunchKernelGGL((accept_finish_kernel<false, false, false>), grid_s, block_s, 0, stream, A);
-    }
+    hipLaunchKernelGGL(finish, dim3((unsigned)Bl), dim3(64 * kFinWaves), 0, stream, A);
     if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
   }
   return SR_OK;
