@@ -23,6 +23,29 @@ int device_cu_count() {
   return n;
 }
 
+// One word per kernel and dynamic LDS size seen: the kernel's address (47
+// bits), the LDS words (13) and the count (4), so that a word is read whole. A
+// slot that two kernels share is overwritten in turn; what does not fit the
+// word is asked for each time. (The query itself takes 0.5 us of a call.)
+int resident_per_cu(const void* fn, int threads, size_t lds) {
+  constexpr int kDevices = 8, kSlots = 64;
+  static std::atomic<uint64_t> cache[kDevices][kSlots];
+  int dev = 0;
+  const uint64_t addr = (uint64_t)(uintptr_t)fn;
+  const bool fits = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kDevices && addr < (1ull << 47) &&
+                    lds % 4 == 0 && lds / 4 < (1u << 13);
+  const uint64_t key = (addr << 17) | ((uint64_t)(lds / 4) << 4);
+  std::atomic<uint64_t>* slot = fits ? &cache[dev][(addr / 16 + lds) % kSlots] : nullptr;
+  if (slot) {
+    const uint64_t w = slot->load(std::memory_order_relaxed);
+    if ((w & ~15ull) == key && (w & 15ull) != 0) return (int)(w & 15ull);
+  }
+  int n = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) != hipSuccess || n < 1) return 1;
+  if (slot && n < 16) slot->store(key | (uint64_t)n, std::memory_order_relaxed);
+  return n;
+}
+
 }  // namespace sr
 
 namespace {

@@ -1997,13 +1997,6 @@ int chunks_per_row(int V, int dtype) {
   return (span + chunk - 1) / chunk;
 }
 
-int resident_per_cu(const void* fn, size_t lds) {
-  int per_cu = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kThreads, lds) != hipSuccess || per_cu < 1)
-    per_cu = 1;
-  return per_cu;
-}
-
 typedef void (*Kernel)(Args);
 template <bool BF16, int NS>
 Kernel sweep_kernel(bool greedy, bool filt) {
@@ -2029,7 +2022,7 @@ Kernel finish_kernel(bool greedy, bool list, bool one) {
 int persistent_grid(const void* fn, long max_tasks, int Bl, int nc) {
   const int cus = device_cu_count();
   if (cus <= 0) return 0;
-  const long cap = (long)cus * resident_per_cu(fn, Bl * sizeof(int));
+  const long cap = (long)cus * resident_per_cu(fn, kThreads, Bl * sizeof(int));
   long grid = cap / nc * nc;
   if (grid == 0) grid = cap;
   if (grid > max_tasks) grid = max_tasks;

@@ -702,12 +702,8 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   plan->q_chunks = (R + rows_per_chunk - 1) / rows_per_chunk;
   const int cus = device_cu_count();
   if (cus <= 0) return SR_ELAUNCH;
-  int per_cu = 1;
   const int threads = plan->qg == 1 ? Shape<1>::kThreads : Shape<kMaxQG>::kThreads;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &per_cu, (const void*)pick_split(D, plan->nq, plan->qg, plan->q_chunks), threads, 0) != hipSuccess ||
-      per_cu < 1)
-    per_cu = 1;
+  const int per_cu = resident_per_cu((const void*)pick_split(D, plan->nq, plan->qg, plan->q_chunks), threads, 0);
   const long pairs = (long)B * Hkv * plan->q_chunks;
   const long target = (long)cus * per_cu;
   // Splits enough for one workgroup per CU: a four-wave workgroup keeps

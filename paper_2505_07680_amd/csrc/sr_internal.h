@@ -331,7 +331,9 @@ int launch_kv_compact(void* k_cache, void* v_cache, uint8_t* cache_mask, int32_t
 int launch_rollback(int32_t* kv_len, uint8_t* cache_mask, const int32_t* new_len,
                     int32_t* phys_len, int B, int L_cap, int32_t* status, hipStream_t stream);
 
-// Cached per-device properties.
+// Cached per-device properties: the compute units, and the workgroups of a
+// kernel that fit one (at least 1).
 int device_cu_count();
+int resident_per_cu(const void* fn, int threads, size_t lds);
 
 }  // namespace sr
