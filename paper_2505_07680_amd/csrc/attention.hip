@@ -536,58 +536,146 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
   if (last_flag == 0u) return;
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 
-  // Each thread owns kItems (row, 4 columns) items and folds the splits in
-  // with a running max, kGroup splits per round of loads.
+  // Merge: out = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s over the splits, M
+  // their largest reference. Bound by the latency of the partials' device-coherent
+  // loads (one to two us a round trip, from another XCD's write), so as many as
+  // registers hold are in flight: first the first kGroup splits' outputs and
+  // every (m, l), then the remaining groups, with the weights from the (m, l) in
+  // LDS. (A running maximum over groups of four splits, their (m, l) beside the
+  // outputs, took 0.33 us per split at 24 rows of 128 columns; this takes
+  // 0.2.) Each thread owns kItems (row, 4 columns) items.
   constexpr int kItems = (QG * MQ * (D / 4) + kT - 1) / kT;
-  constexpr int kGroup = kItems >= 16 ? 1 : (16 / kItems > 8 ? 8 : 16 / kItems);
-  const int n_items = (row_end - row0) * (D / 4);
-  float mx[kItems], den[kItems];
-  floatx4 acc[kItems];
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    mx[k] = kNegInf;
-    den[k] = 0.f;
-    acc[k] = floatx4{0.f, 0.f, 0.f, 0.f};
-  }
-  for (int sp0 = 0; sp0 < ns; sp0 += kGroup) {
-    floatx2 ml2[kGroup][kItems];
-    floatx4 o2[kGroup][kItems];
+  // (registers: 32 to 96, fewer than the key loop's)
+  constexpr int kGroup = kItems >= 3 ? 4 : 8;
+  constexpr int kMlBlock = 64;  // splits whose references sit in LDS at once
+  constexpr int kRows = QG * MQ;
+  static_assert((2 + kMlBlock) * kRows * 4 <= Lds<D, NQ, QG>::kBytes, "the merge's exchange fits");
+  const int n_rows = row_end - row0;
+  const int n_items = n_rows * (D / 4);
+  float* mM = (float*)lds;           // [kRows] M
+  float* mD = mM + kRows;            // [kRows] denominators
+  float* mS = mD + kRows;            // [kMlBlock][kRows] m_s
+  const uint32_t rec0 = (uint32_t)(pair * n_splits * R);
+  const __amdgpu_buffer_rsrc_t rs_none = partial_rsrc(part_o, 0);
+  auto live_row = [&](int row) __attribute__((always_inline)) { return min(row0 + row, Mb - 1); };  // (rows past Mb hold no partial; their result is discarded)
+  // (past the splits: an empty resource, zeros without traffic)
+  auto sp_rsrc = [&](int sp, const __amdgpu_buffer_rsrc_t& rs) __attribute__((always_inline)) { return sp < ns ? rs : rs_none; };
+  auto fetch_o = [&](int sp0, floatx4 (&o2)[kGroup][kItems]) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < kGroup; ++j)
 #pragma unroll
       for (int k = 0; k < kItems; ++k) {
-        const int sp = min(sp0 + j, ns - 1);  // repeats of the last split are discarded below
         const int idx = min(tid + k * kT, n_items - 1);
-        const int r = min(row0 + idx / (D / 4), Mb - 1);  // rows past Mb hold no partial; their result is discarded
-        const uint32_t rec = (uint32_t)((pair * n_splits + sp) * R + r);
-        ml2[j][k] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rs_ml, rec * 8, 0, kDeviceCoherent));
-        o2[j][k] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, (rec * D + (idx % (D / 4)) * 4) * 4, 0, kDeviceCoherent);
+        const uint32_t rec = rec0 + (uint32_t)((sp0 + j) * R + live_row(idx / (D / 4)));
+        o2[j][k] = __builtin_amdgcn_raw_buffer_load_b128(sp_rsrc(sp0 + j, rs_o), (rec * D + (idx % (D / 4)) * 4) * 4, 0, kDeviceCoherent);
       }
+  };
+  auto write_item = [&](int k, const floatx4& sum, float den) __attribute__((always_inline)) {
+    const int idx = tid + k * kT;
+    if (idx >= n_items) return;
+    const int r = row0 + idx / (D / 4);
+    const bool live = r < Mb && den > 0.f;
+    const floatx4 res = live ? sum * (1.f / den) : floatx4{0.f, 0.f, 0.f, 0.f};
+    const int i = r / G, hh = g * G + r % G;
+    *(floatx4*)(out + ((size_t)(b * (gmax + 1) + i) * Hq + hh) * D + (idx % (D / 4)) * 4) = res;
+  };
+  floatx4 o2[kGroup][kItems];
+  fetch_o(0, o2);
+  __builtin_amdgcn_sched_barrier(0);
+  constexpr int kFew = 4;
+  if (kItems <= 4 && ns <= kFew) {  // one round trip: every thread takes its rows' (m, l) itself (0.4 us less than through LDS)
 #pragma unroll
-    for (int j = 0; j < kGroup; ++j) {
-      if (sp0 + j >= ns) break;
+    for (int k = 0; k < (kItems <= 4 ? kItems : 0); ++k) {
+      const int row = live_row(min(tid + k * kT, n_items - 1) / (D / 4));
+      floatx2 x[kFew];
+#pragma unroll
+      for (int j = 0; j < kFew; ++j)
+        x[j] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(sp_rsrc(j, rs_ml), (rec0 + (uint32_t)(j * R + row)) * 8, 0, kDeviceCoherent));
+      float M = kNegInf, den = 0.f;
+#pragma unroll
+      for (int j = 0; j < kFew; ++j) M = j < ns ? fmaxf(M, x[j].x) : M;
+      floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < kFew; ++j) {
+        const float wgt = j < ns && x[j].x != kNegInf ? exp2_hw(x[j].x - M) : 0.f;
+        den += x[j].y * wgt;
+        sum += o2[j][k] * wgt;
+      }
+      write_item(k, sum, den);
+    }
+    return;
+  }
+  // (m, l) of every split: four threads per row take the splits in turn
+  for (int row = tid / 4; row < n_rows; row += kT / 4) {
+    constexpr int kMl = 8;
+    float M = kNegInf, den = 0.f;
+    const uint32_t rec = rec0 + (uint32_t)live_row(row);
+    for (int sp0 = tid % 4; sp0 < ns; sp0 += 4 * kMl) {
+      floatx2 x[kMl];
+#pragma unroll
+      for (int j = 0; j < kMl; ++j)
+        x[j] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(
+                                               rs_ml, sp0 + 4 * j < ns ? (rec + (uint32_t)((sp0 + 4 * j) * R)) * 8 : kOutOfRange, 0, kDeviceCoherent));
+      float Mn = M;
+#pragma unroll
+      for (int j = 0; j < kMl; ++j) Mn = sp0 + 4 * j < ns ? fmaxf(Mn, x[j].x) : Mn;
+      den = Mn == kNegInf ? 0.f : den * exp2_hw(M - Mn);
+#pragma unroll
+      for (int j = 0; j < kMl; ++j) {
+        const int sp = sp0 + 4 * j;
+        if (sp < ns) {
+          if (Mn != kNegInf) den += x[j].y * exp2_hw(x[j].x - Mn);
+          if (sp < kMlBlock) mS[sp * kRows + row] = x[j].x;
+        }
+      }
+      M = Mn;
+    }
+    // the row's four threads (a quad): (M, den) over all splits
+#pragma unroll
+    for (int d = 1; d < 4; d <<= 1) {
+      const float Mo = d == 1 ? perm_f32<dpp::kXor1>(M) : perm_f32<dpp::kXor2>(M);
+      const float Do = d == 1 ? perm_f32<dpp::kXor1>(den) : perm_f32<dpp::kXor2>(den);
+      const float Mn = fmaxf(M, Mo);
+      den = Mn == kNegInf ? 0.f : den * exp2_hw(M - Mn) + Do * exp2_hw(Mo - Mn);
+      M = Mn;
+    }
+    if (tid % 4 == 0) {
+      mM[row] = M;
+      mD[row] = den;
+    }
+  }
+  floatx4 acc[kItems];
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) acc[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+  __syncthreads();
+  for (int b0 = 0; b0 < ns; b0 += kMlBlock) {
+    if (b0 > 0) {  // the next block's references
+      __syncthreads();
+      for (int i = tid; i < min(ns - b0, kMlBlock) * n_rows; i += kT) {
+        const int sp = i / n_rows, row = i % n_rows;
+        mS[sp * kRows + row] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(
+                                                             rs_ml, (rec0 + (uint32_t)((b0 + sp) * R + live_row(row))) * 8, 0, kDeviceCoherent)).x;
+      }
+      __syncthreads();
+    }
+    const int b1 = min(ns, b0 + kMlBlock);
+    for (int sp0 = b0; sp0 < b1; sp0 += kGroup) {
+      if (sp0 > 0) fetch_o(sp0, o2);
 #pragma unroll
       for (int k = 0; k < kItems; ++k) {
-        const float M = fmaxf(mx[k], ml2[j][k].x);
-        if (M == kNegInf) continue;
-        const float ca = exp2f(mx[k] - M);
-        const float cb = exp2f(ml2[j][k].x - M);
-        den[k] = den[k] * ca + ml2[j][k].y * cb;
-        acc[k] = acc[k] * ca + o2[j][k] * cb;
-        mx[k] = M;
+        const int row = min(tid + k * kT, n_items - 1) / (D / 4);
+        const float M = mM[row];
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) {
+          const float m = mS[(sp0 + j < b1 ? sp0 + j - b0 : 0) * kRows + row];
+          const float wgt = sp0 + j < b1 && m != kNegInf ? exp2_hw(m - M) : 0.f;
+          acc[k] += o2[j][k] * wgt;
+        }
       }
     }
   }
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int idx = tid + k * kT;
-    if (idx >= n_items) continue;
-    const int r = row0 + idx / (D / 4);
-    const bool live = r < Mb && den[k] > 0.f;
-    const floatx4 res = live ? acc[k] * (1.f / den[k]) : floatx4{0.f, 0.f, 0.f, 0.f};
-    const int i = r / G, hh = g * G + r % G;
-    *(floatx4*)(out + ((size_t)(b * (gmax + 1) + i) * Hq + hh) * D + (idx % (D / 4)) * 4) = res;
-  }
+  for (int k = 0; k < kItems; ++k) write_item(k, acc[k], mD[min(tid + k * kT, n_items - 1) / (D / 4)]);
 }
 
 typedef void (*SplitKernel)(const uint16_t*, const uint16_t*, const uint16_t*, const uint8_t*,
@@ -706,11 +794,24 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   const int per_cu = resident_per_cu((const void*)pick_split(D, plan->nq, plan->qg, plan->q_chunks), threads, 0);
   const long pairs = (long)B * Hkv * plan->q_chunks;
   const long target = (long)cus * per_cu;
-  // Splits enough for one workgroup per CU: a four-wave workgroup keeps
-  // enough K/V loads in flight to stream at the device's rate, and fewer
-  // splits mean fewer partials to merge (at 16 sequences of 2054 keys, two
-  // splits per (sequence, kv head) measured 30.5 us against 32.7 with four).
-  long splits = ((long)cus + pairs - 1) / pairs;
+  // Splits: the count, up to one workgroup per CU, whose time is least. In
+  // units of a key's time in a workgroup (16 ns at D = 128, a CU's share of HBM):
+  // the keys of a split, times the workgroups the busiest CU gets, and the merge
+  // of each split's partial, 0.2 to 0.35 us or about 16 keys (32 at D = 64 with
+  // one query group, whose keys take less). One sequence of 2048 keys, 32/8 heads
+  // of 128, gamma 5: 24.8 us with the 32 splits that fill the CUs and the merge
+  // of before, 18.8 with the present merge, 16.6 with 11; 12 sequences of 2048,
+  // gamma 0: 28.8 us with 3 splits (288 workgroups for 256 CUs), 23.7 with 2.
+  const long most = ((long)cus + pairs - 1) / pairs;
+  const long per_split = D == 64 && plan->qg == 1 ? 32 : 16;
+  long splits = 1, best = 0;
+  for (long n = 1; n <= most; ++n) {
+    const long t = (pairs * n + cus - 1) / cus * ((L_cap + n - 1) / n) + (n > 1 ? n * per_split : 0);
+    if (n == 1 || t < best) {
+      best = t;
+      splits = n;
+    }
+  }
   // Bound a workgroup's keys, so the last workgroups of a ragged batch do not
   // run long after the rest have finished.
   const long by_length = (L_cap + kMaxSplitKeys - 1) / kMaxSplitKeys;

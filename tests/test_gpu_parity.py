@@ -341,6 +341,31 @@ def test_sharp_softmax_attention(D, G, g, tag, split):
     say(f"sharp d{D} {tag} {split}: B={inp.B} worst relative L2 {worst:.2e}, output RMS {rms:.2f}")
 
 
+# Keys -> cache splits of one (sequence, kv head) pair at D = 128 (about
+# sqrt(keys / 16)): two to four are merged straight from registers, more in
+# groups with their maxima in LDS, more than 64 block by block.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("keys", [130, 300, 700, 4000, 81000])
+@pytest.mark.parametrize("G,gam", [(1, 0), (4, 4), (8, 8)], ids=["1-row", "20-rows", "72-rows"])
+def test_merge_of_any_number_of_splits(D, keys, G, gam):
+    """The splits' partials merged whatever their number, with splits whose
+    keys are all masked among them (Section 4.4, Eq. 8), and the same bits on a
+    second call."""
+    shape = small_shape(name=f"merge-{D}-{keys}-{G}", B=1, Hq=G, Hkv=1, D=D, gamma=(gam, gam), ctx=(keys, keys),
+                        V=1000, seed=keys + G)
+    inp = level_inputs(shape, logits=False)
+    mask = np.zeros((1, inp.k.shape[2]), np.uint8)
+    mask[0, : inp.kv_len[0]] = 1
+    mask[0, keys // 8 : keys // 2] = 0
+    got, st = run_attention(inp, mask=mask)
+    again, _ = run_attention(inp, mask=mask)
+    assert st == 0
+    np.testing.assert_array_equal(got, again)
+    ref, _ = oracle.verify_attention(inp.q, inp.k, inp.v, inp.kv_len, inp.gamma, inp.scale, mask)
+    worst = check_attention(got, ref)
+    say(f"merge d{D} keys={keys} rows={G * (gam + 1)}: worst relative L2 {worst:.2e}")
+
+
 def test_longest_first_dispatch_with_cache_splits():
     """More split workgroups than fit at once, with caches longer than one
     split: the workgroups run in the order of a counting sort of their key
