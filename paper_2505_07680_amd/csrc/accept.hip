@@ -58,8 +58,7 @@
 // the chunk holding u*W re-read and scanned in ascending vocabulary order with
 // its weights computed exactly as in the sweep), the outputs, the rollback,
 // and zeroes every workspace word the sequence's rows used, so the workspace
-// is all zero again when the call ends. The physical length is written by the
-// launch's last finished sequence.
+// is all zero again when the call ends.
 //
 // With top-k or top-p a kernel before the sweep (filter.inc) finds the rows'
 // thresholds. Rows that keep few entries are "listed" there (the entries of
@@ -186,7 +185,6 @@ struct Args {
   double* tva;       // [B][gmax+1][nc][4] each wave's sum |fma(a, rho, -b)| (pair rows), or kSkipped
   float* xlogit;     // [B][gmax+1][4] the draft token's exponent arguments and shifts, p then q (pair rows)
   float* thr;        // [B][gmax+1][2] top-k / top-p thresholds of the p and q rows, or NULL
-  uint32_t* fincnt;  // sequences of this launch finished
   // rows that top-k / top-p leave few entries of (NULL: no such rows are listed)
   uint32_t* smask;   // [B] bit j: the sweep takes position j (its rows are not listed)
   uint32_t* swany;   // non-zero: some bit of smask is set (any launch of the call)
@@ -198,9 +196,8 @@ struct Args {
   int32_t* rb_kv;            // [B] cache lengths, in/out (this launch's sequences)
   uint8_t* rb_mask;          // [B][L_cap] validity mask, or NULL
   int32_t* rb_phys;          // max over all sequences of the new lengths, or NULL
-  const int32_t* rb_kv_all;  // the whole batch's cache lengths (rb_kv - n_before)
   int rb_lcap;
-  int n_before;              // sequences of the call handled by earlier launches
+  bool rb_first;             // the call's first launch: its sweep sets rb_phys to the least value
 };
 
 // Task geometry: each lane holds 16 entries of p (and of q), 32 bytes of
@@ -1004,7 +1001,10 @@ __device__ void write_invalid(const Args& A, int b, uint32_t bits) {
 // exactly as the rollback call does it: a length outside [0, L_cap] or a
 // negative target is flagged and left alone, a target above the length is
 // flagged and ignored; otherwise the mask entries [n, old) are cleared and the
-// length becomes n = min(old, want). `old` is read when the sequence finishes.
+// length becomes n = min(old, want). The physical length (Eq. 9), the maximum of
+// the new lengths over the batch, is an atomic maximum that nothing waits for
+// (the sweep set it to the least value; a counter of finished sequences, whose
+// last one read every length, kept 2 to 3 us at the end of each call).
 __device__ void finish_rollback(const Args& A, int b, int old, int want) {
   if (!A.rb_kv) return;
   const int lane = threadIdx.x & 63;
@@ -1019,29 +1019,9 @@ __device__ void finish_rollback(const Args& A, int b, int old, int want) {
       for (int x = n + lane; x < old; x += 64) A.rb_mask[(size_t)b * A.rb_lcap + x] = 0;
   }
   if (lane == 0) {
-    st_dev((uint32_t*)A.rb_kv + b, (uint32_t)n);
+    A.rb_kv[b] = n;
+    if (A.rb_phys) __hip_atomic_fetch_max(A.rb_phys, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (st && A.status) atomicOr(A.status, st);
-  }
-}
-
-// One wave, after its sequences' rollbacks have completed: count them; the
-// launch's last finished sequence writes the physical length, the maximum of
-// the rolled-back lengths of the whole batch so far (Eq. 9), and resets the
-// counter.
-__device__ void count_finished(const Args& A, uint32_t n) {
-  if (!A.rb_kv || !A.rb_phys || n == 0) return;
-  const int lane = threadIdx.x & 63;
-  stores_done();
-  uint32_t old = 0;
-  if (lane == 0) old = __hip_atomic_fetch_add(A.fincnt, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  old = (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
-  if (old + n != (uint32_t)A.B) return;
-  int m = INT_MIN;
-  for (int b = lane; b < A.n_before + A.B; b += 64) m = max(m, (int)ld_dev((const uint32_t*)A.rb_kv_all + b));
-  m = wave_max_i(m);
-  if (lane == 0) {
-    *A.rb_phys = m;
-    st_dev(A.fincnt, 0u);
   }
 }
 
@@ -1782,7 +1762,6 @@ __device__ void finish_sequence(const Args& A, int b, int gam, const RowOut* row
   if (bits) {
     write_invalid(A, b, bits);
     finish_rollback(A, b, rb_old, kvl);
-    count_finished(A, 1);
     return;
   }
   // outputs
@@ -1803,7 +1782,6 @@ __device__ void finish_sequence(const Args& A, int b, int gam, const RowOut* row
     if (A.new_len) A.new_len[b] = kvl - gam + k;
   }
   finish_rollback(A, b, rb_old, kvl - gam + k);
-  count_finished(A, 1);
 }
 
 // Sequences whose gamma is out of range have no rows: workgroup 0 writes
@@ -1881,6 +1859,7 @@ __global__ void __launch_bounds__(kThreads, NS == 1 ? 3 : 2) accept_kernel(Args 
   extern __shared__ int s_rows[];  // [B] inclusive prefix of live rows
   __shared__ TaskShared sh;
   __shared__ TaskTable tab;
+  if (A.rb_first && blockIdx.x == 0 && threadIdx.x == 0) *A.rb_phys = INT_MIN;
   if (FILT && A.smask && *A.swany == 0u) return;  // every row is listed
   build_row_table(A.gamma, FILT ? A.smask : nullptr, A.gmax, A.B, s_rows);
   const long n_tasks = (long)s_rows[A.B - 1] * A.nc;
@@ -1927,7 +1906,6 @@ __global__ void __launch_bounds__(64 * kFinWaves) accept_finish_kernel(Args A) {
     if (w == 0) {
       write_invalid(A, b, SR_ST_GAMMA);
       finish_rollback(A, b, A.rb_kv ? A.rb_kv[b] : 0, A.kv_len ? A.kv_len[b] : 0);
-      count_finished(A, 1);
     }
     return;
   }
@@ -1974,7 +1952,7 @@ constexpr int kFiltThreads = 1024;
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct Layout {
-  size_t recs, tva, xlogit, thr, fincnt, total;
+  size_t recs, tva, xlogit, thr, total;
 };
 
 Layout layout(int B, int gamma_max, int nc) {
@@ -1984,8 +1962,7 @@ Layout layout(int B, int gamma_max, int nc) {
   L.tva = L.recs + align256(rows * nc * kRecBytes);
   L.xlogit = L.tva + align256(rows * nc * kWaves * sizeof(double));
   L.thr = L.xlogit + align256(rows * 4 * sizeof(float));
-  L.fincnt = L.thr + align256(rows * 2 * sizeof(float));
-  L.total = L.fincnt + 256;
+  L.total = L.thr + align256(rows * 2 * sizeof(float)) + 256;
   return L;
 }
 
@@ -2138,7 +2115,6 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     A.tva = (double*)(ws + L.tva) + r0 * nc * kWaves;
     A.xlogit = (float*)(ws + L.xlogit) + r0 * 4;
     A.thr = filt ? (float*)(ws + L.thr) + r0 * 2 : nullptr;
-    A.fincnt = (uint32_t*)(ws + L.fincnt);
     A.smask = list ? (uint32_t*)(ws + LL.smask) + b0 : nullptr;
     A.swany = list ? (uint32_t*)(ws + LL.smask) + B : nullptr;
     A.rowst = list ? (RowStat*)(ws + LL.rowst) + r0 * 2 : nullptr;
@@ -2148,9 +2124,8 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     A.rb_kv = rollback ? rollback->kv_len + b0 : nullptr;
     A.rb_mask = rollback && rollback->mask ? rollback->mask + (size_t)b0 * rollback->L_cap : nullptr;
     A.rb_phys = rollback ? rollback->phys_len : nullptr;
-    A.rb_kv_all = rollback ? rollback->kv_len : nullptr;
     A.rb_lcap = rollback ? rollback->L_cap : 0;
-    A.n_before = b0;
+    A.rb_first = A.rb_phys && b0 == 0;
     const long max_tasks = (long)Bl * G1 * nc;
     const bool one = nc <= 64;  // chunk records per lane of a row merge
     const Kernel sweep = dtype == SR_BF16 ? sweep_kernel<true>(greedy, filt, one) : sweep_kernel<false>(greedy, filt, one);
