@@ -8,9 +8,9 @@
 // are merged through LDS at the end. Up to 48 query rows, a workgroup is four
 // waves, one per stream, with no workgroup barrier inside the key loop. Up
 // to 96 rows it is eight waves in two query groups: the two waves of a
-// stream each fetch half of every K/V tile into a shared LDS slot (double
-// buffered, one workgroup barrier per tile) and each computes its own group's
-// rows over the whole tile, so the tile is still read once. When the
+// stream each fetch half of every K/V tile into a shared LDS slot (two tiles at
+// a time, a workgroup barrier before and after their compute) and each computes
+// its own group's rows over both, so a tile is still read once. When the
 // cache is split, each split publishes its (max, sum, unnormalised output)
 // partial and bumps a per-(b, g, query chunk) arrival counter; the last
 // workgroup to arrive merges all partials in split order and writes the
@@ -35,8 +35,9 @@
 //   * the softmax reference maximum of a row is raised only when a tile exceeds
 //     it by more than 2^8, so the output accumulators are rarely rescaled;
 //   * P is rounded to bf16 in place: its accumulator layout is exactly the B
-//     operand of O^T += V^T P^T (v_mfma_f32_16x16x16_bf16, K=16 over the keys);
-//     the V^T operand is gathered from LDS with 16-bit reads.
+//     operand of O^T += V^T P^T (v_mfma_f32_16x16x16_bf16, K=16 over the keys;
+//     with two query groups v_mfma_f32_16x16x32_bf16 over two tiles' keys); the
+//     V^T operand comes from the LDS transposing read.
 // Scores are kept in log2 units (scale * log2(e) folded in) and exponentiated
 // with exp2.
 
@@ -261,11 +262,11 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
     }
     st.mbyte = mload[min(kb0 + (lane & (kWaveKeys - 1)), L - 1)];
   };
-  // Ring entry st holds tile j: stage it in LDS buffer buf of the stream's
-  // slot, refill it with the stream's tile kRing further on, compute tile j,
-  // and leave the refilled tile's number in j.
-  auto step = [&](int& j, Stage<D, QG>& st, int buf) __attribute__((always_inline)) {
-    unsigned char* kst = lds + (ws * kBufs + buf) * GG::kWaveBytes;
+  // One query group. Ring entry st holds tile j: stage it in the stream's slot,
+  // refill it with the stream's tile kRing further on, compute tile j, and
+  // leave the refilled tile's number in j.
+  auto step = [&](int& j, Stage<D, QG>& st) __attribute__((always_inline)) {
+    unsigned char* kst = lds + ws * kBufs * GG::kWaveBytes;
     unsigned char* vst = kst + GG::kSlotK;
     const int kb0 = j * kWaveKeys;
     const bool key_ok = lane < kWaveKeys && kb0 + lane < L && (mrow == nullptr || st.mbyte != 0u);
@@ -280,10 +281,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
       *(uint2*)dst = make_uint2(vv.x, vv.y);
       *(uint2*)(dst + 2) = make_uint2(vv.z, vv.w);
     }
-    if constexpr (QG == 1)
-      wave_lds_sync();
-    else
-      __syncthreads();  // both halves of the tile are in the slot
+    wave_lds_sync();
     const int nx = j + kRing * kWaves;
     __builtin_amdgcn_sched_barrier(0);
     fetch(nx, st);  // the ring's other tiles and this refill stay in flight during the compute below
@@ -382,10 +380,129 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
         o[db][qg] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, pb[qg], o[db][qg], 0, 0, 0);
       }
     }
-    // One query group: this tile's LDS reads are issued before the slot is
-    // rewritten. Two: the slot's other buffer takes the next tile, and the
-    // barrier of the step after it orders every read of this one first.
-    if constexpr (QG == 1) wave_lds_sync();
+    wave_lds_sync();  // this tile's LDS reads are issued before the slot is rewritten
+  };
+
+  // Two query groups: two of the stream's tiles at a time. Both are staged (one
+  // LDS buffer each), the query fragments of a k-step are read once for both, the
+  // softmax of a row takes its 32 keys together (one maximum and one sum across
+  // lanes), and the second product runs over 32 keys per instruction: its k
+  // slots lg*8 + e hold the first tile's key lg*4 + e (e < 4) and the second's
+  // lg*4 + e - 4, which is how the scores and the transposed V reads lie in the
+  // registers. (One tile at a time, 16 keys per instruction: 127 us at 4
+  // sequences of 32768 keys, 72 query rows per KV head; now 119.)
+  auto step2 = [&](int& ja, Stage<D, QG>& sa, int& jb, Stage<D, QG>& sb) __attribute__((always_inline)) {
+    unsigned char* kst = lds + (ws * kBufs) * GG::kWaveBytes;
+    uint32_t vb[2];
+    auto stage = [&](int j, Stage<D, QG>& st, int buf) __attribute__((always_inline)) {
+      unsigned char* kd = kst + buf * GG::kWaveBytes;
+      unsigned char* vd = kd + GG::kSlotK;
+      const int kb0 = j * kWaveKeys;
+      const bool key_ok = lane < kWaveKeys && j < j_end && kb0 + lane < L && (mrow == nullptr || st.mbyte != 0u);
+      const uint32_t vbits = (uint32_t)__ballot(key_ok) & 0xffffu;
+      const bool all_rows = vbits == 0xffffu;  // wave-uniform
+#pragma unroll
+      for (int u = 0; u < kLd; ++u) {
+        const int rl = (h * kLd + u) * GG::kRowsPerLoad + lane_row;
+        *(u32x4*)(kd + rl * GG::kKStride + lane_chunk * 16) = st.k[u];
+        const u32x4 vv = (all_rows || ((vbits >> rl) & 1u)) ? st.v[u] : u32x4{0u, 0u, 0u, 0u};
+        uint32_t* dst = (uint32_t*)(vd + rl * GG::kVStride + lane_chunk * 16);
+        *(uint2*)dst = make_uint2(vv.x, vv.y);
+        *(uint2*)(dst + 2) = make_uint2(vv.z, vv.w);
+      }
+      return vbits;
+    };
+    vb[0] = stage(ja, sa, 0);
+    vb[1] = stage(jb, sb, 1);
+    __syncthreads();  // both halves of both tiles are in the slot
+    const int j0 = ja, j1 = jb;
+    ja += kRing * kWaves;
+    jb += kRing * kWaves;
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(ja, sa);  // these and the ring's other tiles stay in flight during the compute below
+    fetch(jb, sb);
+    __builtin_amdgcn_sched_barrier(0);
+    if (j0 < j_end && rbase < Mb) {  // wave-uniform
+      const bool full = (vb[0] & vb[1]) == 0xffffu && j1 * kWaveKeys + kWaveKeys - 1 <= causal0;  // wave-uniform
+      floatx4 sacc[2][NQ];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int qg = 0; qg < NQ; ++qg) sacc[t][qg] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) {
+        const int col = (ks * 32 + lg * 8) * 2;
+        bf16x8 qb[NQ];
+#pragma unroll
+        for (int qg = 0; qg < NQ; ++qg) qb[qg] = *(const bf16x8*)(qst + (h * MQ + qg * 16 + l16) * GG::kKStride + col);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const bf16x8 ka = *(const bf16x8*)(kst + t * GG::kWaveBytes + l16 * GG::kKStride + col);
+#pragma unroll
+          for (int qg = 0; qg < NQ; ++qg) sacc[t][qg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qb[qg], sacc[t][qg], 0, 0, 0);
+        }
+      }
+      bf16x8 pb[NQ];
+#pragma unroll
+      for (int qg = 0; qg < NQ; ++qg) {
+        pb[qg] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        if (rbase + qg * 16 < Mb) {
+          const int r = rbase + qg * 16 + l16;
+          float sc[8];
+          float mt = kNegInf;
+          if (full) {  // every row sees all 32 keys (see the single-tile step)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              sc[e] = sacc[e / 4][qg][e % 4];
+              mt = fmaxf(mt, sc[e]);
+            }
+            mt *= scale_log2;
+          } else {
+            const int lim = r < Mb ? causal0 + r / G : -1;  // last key this query row sees
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const int kl = lg * 4 + e % 4;
+              const int kb0 = (e < 4 ? j0 : j1) * kWaveKeys;
+              const bool vis = ((vb[e / 4] >> kl) & 1u) && (kb0 + kl <= lim);
+              sc[e] = vis ? sacc[e / 4][qg][e % 4] * scale_log2 : kNegInf;
+              mt = fmaxf(mt, sc[e]);
+            }
+          }
+          mt = max_across_rows(mt);
+          const bool grow = mt > m_run[qg] + kLazy;
+          const float mref = grow ? mt : m_run[qg];
+          const float alpha = m_run[qg] == mref ? 1.f : exp2_hw(m_run[qg] - mref);
+          const float mr = mref == kNegInf ? 0.f : mref;
+          float pk[8];
+          float ls = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            pk[e] = exp2_hw(full ? fmaf(sc[e], scale_log2, -mr) : sc[e] - mr);
+            ls += pk[e];
+          }
+          ls = sum_across_rows(ls);
+          l_run[qg] = l_run[qg] * alpha + ls;
+          m_run[qg] = mref;
+          if (__ballot(grow) != 0ull) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o[db][qg] *= alpha;
+          }
+          pb[qg] = __builtin_bit_cast(bf16x8, u32x4{pack_bf16x2(pk[0], pk[1]), pack_bf16x2(pk[2], pk[3]),
+                                                    pack_bf16x2(pk[4], pk[5]), pack_bf16x2(pk[6], pk[7])});
+        }
+      }
+      typedef short shortx8 __attribute__((ext_vector_type(8)));
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const unsigned char* vrow = kst + GG::kSlotK + (lg * 4 + (l16 >> 2)) * GG::kVStride + (db * 16 + (l16 & 3) * 4) * 2;
+        const shortx4 va0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)vrow);
+        const shortx4 va1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)(vrow + GG::kWaveBytes));
+        const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(va0, va1, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+        for (int qg = 0; qg < NQ; ++qg) o[db][qg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[qg], o[db][qg], 0, 0, 0);
+      }
+    }
+    __syncthreads();  // every read of the two buffers came before the next tiles
   };
 
   // Issue order: this workgroup's query rows, then the ring; the query rows
@@ -429,13 +546,13 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
   if constexpr (QG == 1) {
     while (jr[0] < j_end) {
 #pragma unroll
-      for (int r = 0; r < kRing; ++r) step(jr[r], ring[r], 0);
+      for (int r = 0; r < kRing; ++r) step(jr[r], ring[r]);
     }
   } else {
     const int rounds = (j_end - first0 + kRing * kWaves - 1) / (kRing * kWaves);
     for (int it = 0; it < rounds; ++it) {
 #pragma unroll
-      for (int r = 0; r < kRing; ++r) step(jr[r], ring[r], r % kBufs);
+      for (int r = 0; r < kRing; r += 2) step2(jr[r], ring[r], jr[r + 1], ring[r + 1]);
     }
   }
   __syncthreads();
