@@ -164,7 +164,8 @@ int specrouter_verify_attention(const void* q, const void* k_cache, const void* 
  *               j >= gamma_b (and all entries of a bad sequence) are NaN
  * workspace     device scratch of specrouter_accept_workspace_size() bytes (part
  *               of them room for what top-k / top-p keep: with less, such
- *               calls work through every logit instead); it must be zero-filled before its FIRST use and every call leaves
+ *               calls work through every logit instead); it must be
+ *               zero-filled before its FIRST use and every call leaves
  *               it zero-filled again, whatever shape the next call has (each
  *               call clears every word it wrote)
  * Logits must be finite or -inf, with |logit| / T < 2^23; a row that is

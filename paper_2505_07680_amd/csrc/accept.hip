@@ -38,12 +38,16 @@
 //     its first pass) and re-loads them until all are present (for at most
 //     about 200 us, then the task gives up, see below); it merges them into
 //     the row's normalisers in a fixed order (fp64); each wave forms its own
-//     factors f_p = 2^(r_w - r_max)/S_p, f_q likewise, from its own shifts
-//     r_w (integers, so 2^(r_w - r_max) is exact; 1/S from the hardware
-//     reciprocal estimate and two Newton steps); the lanes then sum |P - Q|
-//     over their entries, scaled so that one of the two factors is 1
-//     (fma(a, rho, -b) with rho = min/max of the factors), and each wave
-//     publishes its part.
+//     factor c = f_p/f_q from its own shifts (f_p = 2^(r_w - r_max)/S_p, f_q
+//     likewise; integers, so 2^(r_w - r_max) is exact; 1/S_p from the hardware
+//     reciprocal estimate and two Newton steps); the lanes then sum
+//     |e_p c - e_q| over their entries, in units of f_q, and each wave
+//     publishes its part scaled back.
+// The sampling sweep is bound by its vector instructions, not by HBM: one factor
+// and one fma and add per entry in the TV sum, one fma per entry for the KL
+// numerator, maxima of two entries per instruction and wave reductions of one
+// instruction per step took 256 ragged sequences (gamma 1..8, bf16, V 128256)
+// from 242 to 198 us a call, 16 sequences of gamma 5, fp32, from 38.3 to 35.1.
 // Waiting is bounded: a task whose row is not complete after the time limit
 // publishes a "skipped" mark instead of its sum, and the row's finaliser
 // recomputes that chunk's sum from memory with the same arithmetic. No
@@ -182,7 +186,7 @@ struct Args {
   float lg;                 // log2(e) / T: softmax(z / T) entries are 2^(z lg - r)
   // workspace
   u32x4* recs;       // [B][gmax+1][nc] records, two 16-byte words each
-  double* tva;       // [B][gmax+1][nc][4] each wave's sum |fma(a, rho, -b)| (pair rows), or kSkipped
+  double* tva;       // [B][gmax+1][nc][4] each wave's sum |e_p c - e_q|, scaled (pair rows), or kSkipped
   float* xlogit;     // [B][gmax+1][4] the draft token's exponent arguments and shifts, p then q (pair rows)
   float* thr;        // [B][gmax+1][2] top-k / top-p thresholds of the p and q rows, or NULL
   // rows that top-k / top-p leave few entries of (NULL: no such rows are listed)
