@@ -41,6 +41,8 @@
 // Scores are kept in log2 units (scale * log2(e) folded in) and exponentiated
 // with exp2.
 
+#include <math.h>
+
 #include "sr_internal.h"
 
 namespace sr {
@@ -56,7 +58,7 @@ constexpr int kWaveKeys = 16;
 // than 96 rows go to further query chunks, which read the same K/V again.
 constexpr int kMaxNQ = 3;
 constexpr int kMaxQG = 2;
-constexpr float kLazy = 8.f;  // log2 headroom of the lazily rescaled softmax reference
+constexpr float kLazy = 8.f;  // log2 headroom of the lazily rescaled softmax reference (AttentionPlan::lazy where splits are few)
 // Arrival counters sit one per 128-byte line: the splits of different
 // (sequence, kv head, query chunk) jobs then never contend for one line.
 constexpr int kCounterStride = 32;
@@ -147,7 +149,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
                   float* __restrict__ out, float* __restrict__ part_o,
                   float* __restrict__ part_ml, uint32_t* __restrict__ counters,
                   const int32_t* __restrict__ order, int B, int gmax, int Hq, int Hkv, int L_cap,
-                  float scale_log2, int split_keys, int n_splits, int q_chunks,
+                  float scale_log2, float lazy, int split_keys, int n_splits, int q_chunks,
                   int32_t* __restrict__ status) {
   using GG = Geo<D>;
   constexpr int MQ = 16 * NQ;
@@ -336,12 +338,12 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
         }
         mt = max_across_rows(mt);
         // Lazy rescaling: a row keeps its reference maximum until a tile
-        // exceeds it by more than kLazy (log2 units), so P stays below
-        // 2^kLazy and the output accumulators are rescaled only then
+        // exceeds it by more than lazy (log2 units; kLazy, unless the plan
+        // has fewer splits), so P stays below 2^kLazy and the output accumulators are rescaled only then
         // (skipped by the whole wave when no row needs it).
         // (straight-line: every exponential is computed and selected, no
         // per-entry branches)
-        const bool grow = mt > m_run[qg] + kLazy;
+        const bool grow = mt > m_run[qg] + lazy;
         const float mref = grow ? mt : m_run[qg];
         // exp2(-inf) = 0 covers a first reference (the old one -inf); equal
         // references, -inf ones included, give 1
@@ -469,7 +471,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
             }
           }
           mt = max_across_rows(mt);
-          const bool grow = mt > m_run[qg] + kLazy;
+          const bool grow = mt > m_run[qg] + lazy;
           const float mref = grow ? mt : m_run[qg];
           const float alpha = m_run[qg] == mref ? 1.f : exp2_hw(m_run[qg] - mref);
           const float mr = mref == kNegInf ? 0.f : mref;
@@ -797,7 +799,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
 
 typedef void (*SplitKernel)(const uint16_t*, const uint16_t*, const uint16_t*, const uint8_t*,
                             const int32_t*, const int32_t*, float*, float*, float*, uint32_t*,
-                            const int32_t*, int, int, int, int, int, float, int, int, int, int32_t*);
+                            const int32_t*, int, int, int, int, int, float, float, int, int, int, int32_t*);
 
 // The dispatch order of the split workgroups when there are more than fit on
 // the device at once (one workgroup of kOrderThreads): every job (sequence,
@@ -921,10 +923,15 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   // gamma 0: 28.8 us with 3 splits (288 workgroups for 256 CUs), 23.7 with 2.
   const long most = ((long)cus + pairs - 1) / pairs;
   const long per_split = D == 64 && plan->qg == 1 ? 32 : 16;
-  long splits = 1, best = 0;
-  for (long n = 1; n <= most; ++n) {
+  // With two query groups a softmax reference serves up to two tiles of a wave, so
+  // where one workgroup per CU leaves a wave one tile (64 keys per split), the
+  // splits stay that short (see lazy below).
+  constexpr long kTileKeys = kWaves * kWaveKeys;
+  const long least = plan->qg == 1 || L_cap > most * kTileKeys ? 1 : (L_cap + kTileKeys - 1) / kTileKeys;
+  long splits = least, best = 0;
+  for (long n = least; n <= most; ++n) {
     const long t = (pairs * n + cus - 1) / cus * ((L_cap + n - 1) / n) + (n > 1 ? n * per_split : 0);
-    if (n == 1 || t < best) {
+    if (n == least || t < best) {
       best = t;
       splits = n;
     }
@@ -945,6 +952,14 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   sk = (sk + kWaveKeys - 1) / kWaveKeys * kWaveKeys;
   plan->split_keys = sk;
   plan->n_splits = (L_cap + sk - 1) / sk;
+  // The key that a reference was taken from has P = 1, without rounding: one per
+  // wave with a lazy reference. Fewer and longer splits would have fewer of
+  // them (64 to 8192 normal keys: 1.05e-3 off the 64-bit result with one tile
+  // per wave, 1.5e-3 with three), so there the reference follows every tile's
+  // maximum, down by 8 at most and by 32 in all (1.05e-3 again; sums stay below
+  // 2^32 times their value).
+  const int tiles = sk / (kWaves * kWaveKeys) + 1;
+  plan->lazy = splits < most ? -fminf(8.f, 32.f / (float)tiles) : kLazy;
   // [arrival counters: B*Hkv*q_chunks, one per 128-byte line][partial o][partial (m, l)][order]
   const size_t counters = (size_t)B * Hkv * plan->q_chunks * kCounterStride * sizeof(uint32_t);
   plan->part_offset = counters;
@@ -978,7 +993,7 @@ int launch_verify_attention(const void* q, const void* k_cache, const void* v_ca
   hipLaunchKernelGGL(pick_split(D, plan.nq, plan.qg, plan.q_chunks), grid, dim3(threads), 0, stream,
                      (const uint16_t*)q, (const uint16_t*)k_cache, (const uint16_t*)v_cache,
                      cache_mask, kv_len, gamma, out, part_o, part_ml, counters, order, B, gamma_max, Hq,
-                     Hkv, L_cap, scale * kLog2e, plan.split_keys, plan.n_splits, plan.q_chunks, status);
+                     Hkv, L_cap, scale * kLog2e, plan.lazy, plan.split_keys, plan.n_splits, plan.q_chunks, status);
   if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
   return SR_OK;
 }

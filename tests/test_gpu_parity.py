@@ -366,6 +366,27 @@ def test_merge_of_any_number_of_splits(D, keys, G, gam):
     say(f"merge d{D} keys={keys} rows={G * (gam + 1)}: worst relative L2 {worst:.2e}")
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,gam,keys", [(32, 8, 128, 5, 2048), (4, 4, 64, 3, 900), (32, 2, 64, 8, 1500), (64, 8, 128, 8, 1000)])
+def test_short_batches_round_no_more_than_one_tile_per_wave(Hq, Hkv, D, gam, keys):
+    """One sequence, fewer and longer splits than there are CUs: the error of P's
+    rounding to bf16 stays that of one 16-key tile per wave, whose largest
+    key has P = 1 without rounding. For normal scores of unit variance that
+    is 1.0e-3 to 1.06e-3 of the output (numpy, 64 to 8192 keys, 400 rows each), and
+    1.4e-3 or more with one such key per two tiles; the bound lies between."""
+    shape = small_shape(name=f"short-{D}-{keys}-{Hq}", B=1, Hq=Hq, Hkv=Hkv, D=D, gamma=(gam, gam), ctx=(keys, keys),
+                        V=1000, seed=keys)
+    inp = level_inputs(shape, logits=False)
+    r = np.random.default_rng(keys)
+    for x in (inp.q, inp.k, inp.v):
+        x[...] = bf16_bits_from_f32(r.standard_normal(x.shape).astype(np.float32))
+    got, st = run_attention(inp)
+    assert st == 0
+    ref, _ = oracle.verify_attention(inp.q, inp.k, inp.v, inp.kv_len, inp.gamma, inp.scale)
+    err = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    say(f"short d{D} keys={keys} heads={Hq}/{Hkv}: relative L2 {err:.2e}")
+    assert err < 1.2e-3
+
+
 def test_longest_first_dispatch_with_cache_splits():
     """More split workgroups than fit at once, with caches longer than one
     split: the workgroups run in the order of a counting sort of their key
