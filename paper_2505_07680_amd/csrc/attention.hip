@@ -32,16 +32,17 @@
 //   * S^T = K Q^T on MFMA (v_mfma_f32_16x16x32_bf16: 16 keys x 16 queries per
 //     block, K=32 over the head dimension); each lane then holds 4 scores of
 //     ONE query, so the softmax max/sum need only two cross-lane steps;
-//   * the softmax reference maximum of a row is raised only when a tile exceeds
-//     it by more than 2^8, so the output accumulators are rarely rescaled;
+//   * the softmax reference of a row is raised to a tile's maximum only when
+//     that exceeds it by more than 2^8, so the output accumulators are rarely
+//     rescaled; where the plan has fewer splits than one workgroup per CU it
+//     also moves within one binade with every tile (see next_ref and
+//     attention_plan), which rescales them by less than 2 each time;
 //   * P is rounded to bf16 in place: its accumulator layout is exactly the B
 //     operand of O^T += V^T P^T (v_mfma_f32_16x16x16_bf16, K=16 over the keys;
 //     with two query groups v_mfma_f32_16x16x32_bf16 over two tiles' keys); the
 //     V^T operand comes from the LDS transposing read.
 // Scores are kept in log2 units (scale * log2(e) folded in) and exponentiated
 // with exp2.
-
-#include <math.h>
 
 #include "sr_internal.h"
 
@@ -58,7 +59,10 @@ constexpr int kWaveKeys = 16;
 // than 96 rows go to further query chunks, which read the same K/V again.
 constexpr int kMaxNQ = 3;
 constexpr int kMaxQG = 2;
-constexpr float kLazy = 8.f;  // log2 headroom of the lazily rescaled softmax reference (AttentionPlan::lazy where splits are few)
+// How far (log2) a tile's maximum exceeds a row's softmax reference before that
+// is raised, and the same where it follows the tiles.
+constexpr float kLazy = 8.f;
+constexpr float kLazyFollow = 7.f;
 // Arrival counters sit one per 128-byte line: the splits of different
 // (sequence, kv head, query chunk) jobs then never contend for one line.
 constexpr int kCounterStride = 32;
@@ -139,9 +143,26 @@ struct Stage {  // one wave's part of a 16-key tile in flight
   uint32_t mbyte;  // validity byte of key (lane mod 16), evaluated when consumed
 };
 
+// A row's softmax reference (log2 units) for a tile whose largest score is mt,
+// m_run being the one before; grow: mt is far above that (or the row's first).
+// Lazy: the reference stays unless it grows, to mt. Following (FOLLOW): it takes
+// mt's fraction, so that the tile's largest key, a whole number of units away,
+// has P = a power of two, which bf16 holds without rounding. It keeps its whole
+// part, one above that of the score it was last raised to, so it is always
+// above that score: in either mode P stays below 2^8 and the accumulators
+// below 2^8 times the sum of what they hold, however the tiles' maxima fall.
+template <bool FOLLOW>
+__device__ __forceinline__ float next_ref(float mt, float m_run, bool grow) {
+  if constexpr (!FOLLOW) return grow ? mt : m_run;
+  const float whole = floorf(m_run);
+  const float t = whole + __builtin_amdgcn_fractf(mt);
+  const float moved = t - whole < 1.f ? t : whole;  // (a sum that was rounded up)
+  return grow ? mt + 1.f : mt == kNegInf ? m_run : moved;
+}
+
 // Waves per SIMD the register allocation must allow: three for one row block
 // (168 registers), else two (256).
-template <int D, int NQ, int QG, bool NT>
+template <int D, int NQ, int QG, bool NT, bool FOLLOW>
 __global__ void __launch_bounds__(Shape<QG>::kThreads, NQ == 1 && QG == 1 ? 3 : 2)
 attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
                   const uint16_t* __restrict__ vc, const uint8_t* __restrict__ mask,
@@ -149,7 +170,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
                   float* __restrict__ out, float* __restrict__ part_o,
                   float* __restrict__ part_ml, uint32_t* __restrict__ counters,
                   const int32_t* __restrict__ order, int B, int gmax, int Hq, int Hkv, int L_cap,
-                  float scale_log2, float lazy, int split_keys, int n_splits, int q_chunks,
+                  float scale_log2, int split_keys, int n_splits, int q_chunks,
                   int32_t* __restrict__ status) {
   using GG = Geo<D>;
   constexpr int MQ = 16 * NQ;
@@ -337,14 +358,12 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
           }
         }
         mt = max_across_rows(mt);
-        // Lazy rescaling: a row keeps its reference maximum until a tile
-        // exceeds it by more than lazy (log2 units; kLazy, unless the plan
-        // has fewer splits), so P stays below 2^kLazy and the output accumulators are rescaled only then
-        // (skipped by the whole wave when no row needs it).
+        // P stays below 2^kLazy; the output accumulators are rescaled only
+        // when the reference moves (skipped by the whole wave when no row's does).
         // (straight-line: every exponential is computed and selected, no
         // per-entry branches)
-        const bool grow = mt > m_run[qg] + lazy;
-        const float mref = grow ? mt : m_run[qg];
+        const bool grow = mt > m_run[qg] + (FOLLOW ? kLazyFollow : kLazy);
+        const float mref = next_ref<FOLLOW>(mt, m_run[qg], grow);
         // exp2(-inf) = 0 covers a first reference (the old one -inf); equal
         // references, -inf ones included, give 1
         const float alpha = m_run[qg] == mref ? 1.f : exp2_hw(m_run[qg] - mref);
@@ -359,7 +378,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
         ls = sum_across_rows(ls);
         l_run[qg] = l_run[qg] * alpha + ls;
         m_run[qg] = mref;
-        if (__ballot(grow) != 0ull) {
+        if (FOLLOW || __ballot(grow) != 0ull) {
 #pragma unroll
           for (int db = 0; db < DB; ++db) o[db][qg] *= alpha;
         }
@@ -471,8 +490,8 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
             }
           }
           mt = max_across_rows(mt);
-          const bool grow = mt > m_run[qg] + lazy;
-          const float mref = grow ? mt : m_run[qg];
+          const bool grow = mt > m_run[qg] + (FOLLOW ? kLazyFollow : kLazy);
+          const float mref = next_ref<FOLLOW>(mt, m_run[qg], grow);
           const float alpha = m_run[qg] == mref ? 1.f : exp2_hw(m_run[qg] - mref);
           const float mr = mref == kNegInf ? 0.f : mref;
           float pk[8];
@@ -485,7 +504,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
           ls = sum_across_rows(ls);
           l_run[qg] = l_run[qg] * alpha + ls;
           m_run[qg] = mref;
-          if (__ballot(grow) != 0ull) {
+          if (FOLLOW || __ballot(grow) != 0ull) {
 #pragma unroll
             for (int db = 0; db < DB; ++db) o[db][qg] *= alpha;
           }
@@ -799,7 +818,7 @@ attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
 
 typedef void (*SplitKernel)(const uint16_t*, const uint16_t*, const uint16_t*, const uint8_t*,
                             const int32_t*, const int32_t*, float*, float*, float*, uint32_t*,
-                            const int32_t*, int, int, int, int, int, float, float, int, int, int, int32_t*);
+                            const int32_t*, int, int, int, int, int, float, int, int, int, int32_t*);
 
 // The dispatch order of the split workgroups when there are more than fit on
 // the device at once (one workgroup of kOrderThreads): every job (sequence,
@@ -873,21 +892,22 @@ attn_order_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict_
   for (int item = tid + kOrderKept * kOrderThreads; item < n_items; item += kOrderThreads) place(item, bucket(item));
 }
 
-template <int D>
+template <int D, bool FOLLOW>
 SplitKernel pick_split(int nq, int qg, int q_chunks) {
   if (qg == 1) {
     switch (nq) {
-      case 1: return attn_split_kernel<D, 1, 1, true>;
-      case 2: return attn_split_kernel<D, 2, 1, true>;
-      default: return attn_split_kernel<D, 3, 1, true>;
+      case 1: return attn_split_kernel<D, 1, 1, true, FOLLOW>;
+      case 2: return attn_split_kernel<D, 2, 1, true, FOLLOW>;
+      default: return attn_split_kernel<D, 3, 1, true, FOLLOW>;
     }
   }
-  if (nq == 2) return attn_split_kernel<D, 2, 2, true>;
-  return q_chunks == 1 ? attn_split_kernel<D, 3, 2, true> : attn_split_kernel<D, 3, 2, false>;
+  if (nq == 2) return attn_split_kernel<D, 2, 2, true, FOLLOW>;
+  return q_chunks == 1 ? attn_split_kernel<D, 3, 2, true, FOLLOW> : attn_split_kernel<D, 3, 2, false, FOLLOW>;
 }
 
-SplitKernel pick_split(int D, int nq, int qg, int q_chunks) {
-  return D == 64 ? pick_split<64>(nq, qg, q_chunks) : pick_split<128>(nq, qg, q_chunks);
+SplitKernel pick_split(int D, int nq, int qg, int q_chunks, bool follow) {
+  if (follow) return D == 64 ? pick_split<64, true>(nq, qg, q_chunks) : pick_split<128, true>(nq, qg, q_chunks);
+  return D == 64 ? pick_split<64, false>(nq, qg, q_chunks) : pick_split<128, false>(nq, qg, q_chunks);
 }
 
 }  // namespace
@@ -910,7 +930,7 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   const int cus = device_cu_count();
   if (cus <= 0) return SR_ELAUNCH;
   const int threads = plan->qg == 1 ? Shape<1>::kThreads : Shape<kMaxQG>::kThreads;
-  const int per_cu = resident_per_cu((const void*)pick_split(D, plan->nq, plan->qg, plan->q_chunks), threads, 0);
+  const int per_cu = resident_per_cu((const void*)pick_split(D, plan->nq, plan->qg, plan->q_chunks, false), threads, 0);
   const long pairs = (long)B * Hkv * plan->q_chunks;
   const long target = (long)cus * per_cu;
   // Splits: the count, up to one workgroup per CU, whose time is least. In
@@ -925,7 +945,7 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   const long per_split = D == 64 && plan->qg == 1 ? 32 : 16;
   // With two query groups a softmax reference serves up to two tiles of a wave, so
   // where one workgroup per CU leaves a wave one tile (64 keys per split), the
-  // splits stay that short (see lazy below).
+  // splits stay that short (see follow below).
   constexpr long kTileKeys = kWaves * kWaveKeys;
   const long least = plan->qg == 1 || L_cap > most * kTileKeys ? 1 : (L_cap + kTileKeys - 1) / kTileKeys;
   long splits = least, best = 0;
@@ -955,11 +975,9 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   // The key that a reference was taken from has P = 1, without rounding: one per
   // wave with a lazy reference. Fewer and longer splits would have fewer of
   // them (64 to 8192 normal keys: 1.05e-3 off the 64-bit result with one tile
-  // per wave, 1.5e-3 with three), so there the reference follows every tile's
-  // maximum, down by 8 at most and by 32 in all (1.05e-3 again; sums stay below
-  // 2^32 times their value).
-  const int tiles = sk / (kWaves * kWaveKeys) + 1;
-  plan->lazy = splits < most ? -fminf(8.f, 32.f / (float)tiles) : kLazy;
+  // per wave, 1.5e-3 with three), so there the reference follows the tiles
+  // (one such key per tile whatever the length: 1.05e-3 again).
+  plan->follow = splits < most ? 1 : 0;
   // [arrival counters: B*Hkv*q_chunks, one per 128-byte line][partial o][partial (m, l)][order]
   const size_t counters = (size_t)B * Hkv * plan->q_chunks * kCounterStride * sizeof(uint32_t);
   plan->part_offset = counters;
@@ -990,10 +1008,10 @@ int launch_verify_attention(const void* q, const void* k_cache, const void* v_ca
                        Hkv, plan.q_chunks, L_cap, plan.split_keys, plan.n_splits, order);
     if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
   }
-  hipLaunchKernelGGL(pick_split(D, plan.nq, plan.qg, plan.q_chunks), grid, dim3(threads), 0, stream,
+  hipLaunchKernelGGL(pick_split(D, plan.nq, plan.qg, plan.q_chunks, plan.follow != 0), grid, dim3(threads), 0, stream,
                      (const uint16_t*)q, (const uint16_t*)k_cache, (const uint16_t*)v_cache,
                      cache_mask, kv_len, gamma, out, part_o, part_ml, counters, order, B, gamma_max, Hq,
-                     Hkv, L_cap, scale * kLog2e, plan.lazy, plan.split_keys, plan.n_splits, plan.q_chunks, status);
+                     Hkv, L_cap, scale * kLog2e, plan.split_keys, plan.n_splits, plan.q_chunks, status);
   if (hipGetLastError() != hipSuccess) return SR_ELAUNCH;
   return SR_OK;
 }

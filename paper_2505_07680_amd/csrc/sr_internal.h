@@ -270,7 +270,7 @@ struct AttentionPlan {
   int q_chunks;    // workgroups along the query rows of one (sequence, kv head)
   int split_keys;  // keys per split (multiple of 32)
   int n_splits;    // splits along the cache
-  float lazy;      // how far (log2) a tile's maximum exceeds a row's softmax reference before that moves
+  int follow;      // the softmax references follow the tiles
   size_t part_offset;  // byte offset of the split partials in the workspace
   int ordered;         // more workgroups than fit at once: dispatched longest job first
   size_t order_offset;  // byte offset of the dispatch order in the workspace

@@ -387,6 +387,39 @@ def test_short_batches_round_no_more_than_one_tile_per_wave(Hq, Hkv, D, gam, key
     assert err < 1.2e-3
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G,gam", [(1, 0), (8, 8)], ids=["1-row", "72-rows"])
+@pytest.mark.parametrize("course", ["falling", "rising", "zigzag"])
+def test_scores_that_drift_leave_the_headroom_of_large_values(D, G, gam, course):
+    """Scores that move by 3 log2 units from one 64-key group (a tile of every
+    wave) to the next, with values so large that little is left below fp32's
+    2^128: a wave's sum of P v is below 2^5 times the values while its scores
+    fall from the reference, and below 2^8 times that where they rise above
+    it, however the reference follows them."""
+    keys, scale = 4000, 0.125
+    big = 2.0**112 if course == "rising" else 2.0**118
+    shape = small_shape(name=f"drift-{D}-{G}", B=1, Hq=G, Hkv=1, D=D, gamma=(gam, gam), ctx=(keys, keys), V=1000,
+                        seed=keys + D + G)
+    inp = level_inputs(shape, logits=False)
+    inp.scale = scale
+    group = np.arange(inp.k.shape[2]) // 64
+    level = {"falling": -3 * group, "rising": 3 * group, "zigzag": -3 * (group % 24)}[course]
+    q = np.zeros(inp.q.shape, np.float32)
+    q[..., 0] = 1.0
+    k = 0.02 * f32_from_bf16_bits(inp.k)  # (only the first column meets q)
+    k[..., 0] += level[None, None, :] * np.log(2.0) / scale
+    with np.errstate(over="ignore"):  # (rows past the length hold anything)
+        v = f32_from_bf16_bits(inp.v) * big
+    inp.q, inp.k, inp.v = (bf16_bits_from_f32(x.astype(np.float32)) for x in (q, k, v))
+    got, st = run_attention(inp)
+    assert st == 0
+    assert np.isfinite(got).all()
+    inp.v = bf16_bits_from_f32((f32_from_bf16_bits(inp.v) / big).astype(np.float32))
+    ref, _ = oracle.verify_attention(inp.q, inp.k, inp.v, inp.kv_len, inp.gamma, inp.scale)
+    worst = check_attention(got * np.float32(1 / big), ref)
+    say(f"drift d{D} {course} rows={G * (gam + 1)}: worst relative L2 {worst:.2e}")
+
+
 def test_longest_first_dispatch_with_cache_splits():
     """More split workgroups than fit at once, with caches longer than one
     split: the workgroups run in the order of a counting sort of their key
