@@ -779,14 +779,15 @@ __device__ __forceinline__ void argmax_pass(const Args& A, const TaskInfo& t, co
 // An entry of a listed row: the exponent argument x = z lg - r rounded to 32
 // bits, its exponential, and what the rounding of x left out (the whole row
 // shares one shift, so x of a small entry is rounded coarsely; the correction
-// to first order leaves the exponential's own error, about 1e-7).
+// to first order leaves the exponential's own error, about 1e-7; 0 where x is
+// -inf, as for a mask of the type's lowest value, whose exponential is 0).
 struct ListEnt {
   float x, e;
   double d;
   __device__ __forceinline__ ListEnt(float z, float lg, float r) {
     x = fmaf(z, lg, -r);
     e = exp2_hw(x);
-    d = fma((double)z, (double)lg, -(double)r) - (double)x;
+    d = x == kNegInf ? 0.0 : fma((double)z, (double)lg, -(double)r) - (double)x;
   }
   __device__ __forceinline__ double val() const { return fma((double)e, kLn2 * d, (double)e); }
 };

@@ -94,6 +94,32 @@ def test_listed_rows_match_reference(logits, V, top_k, top_p):
         say(f"  ok ({nf} filter-boundary skipped, {nb} boundary, {nbm} differ)")
 
 
+LOWEST = {"f32": np.float32(-3.4028234663852886e38), "bf16": np.float32(-3.3895313892515355e38)}
+
+
+@pytest.mark.parametrize("logits", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [60, 200, 4101])
+@pytest.mark.parametrize("top_k,top_p", [(50, 1.0), (0, 0.9), (50, 0.9)])
+def test_masks_of_the_lowest_value_match_reference(logits, V, top_k, top_p):
+    """Most of the vocabulary masked with the type's lowest value rather than
+    -inf (fewer entries left than top-k asks for, or just about as many):
+    masked entries that the filter keeps have probability 0."""
+    inp = level_inputs(small_shape(name=f"lowest-{logits}-{V}", B=4, V=V, gamma=(3, 5), seed=900 + V), kv=False)
+    rng = np.random.default_rng(V)
+    masked = rng.random(V) < (0.6 if V == 60 else 0.9)
+    p, q = (np.where(masked, LOWEST[logits], x.astype(np.float32)) for x in (inp.p_logits, inp.q_logits))
+    drafts = np.argmax(q + rng.gumbel(size=q.shape), axis=-1).astype(np.int32)
+    if logits == "bf16":
+        p, q = bf16_bits_from_f32(p), bf16_bits_from_f32(q)
+    say(f"lowest {logits} V={V} top_k={top_k} top_p={top_p} ({int((~masked).sum())} entries not masked)")
+    got = run_accept(None, None, drafts, inp.gamma, inp.u_acc, inp.u_res, p_dev=_padded(p), q_dev=_padded(q),
+                     temperature=0.8, top_k=top_k, top_p=top_p)
+    ref = oracle.accept_and_diverge(p, q, drafts, inp.gamma, inp.u_acc, inp.u_res, temperature=0.8, top_k=top_k,
+                                    top_p=top_p)
+    assert got["status"] == ref["status"] == 0
+    _check_filtered(got, ref)
+
+
 @pytest.mark.parametrize("logits", ["f32", "bf16"])
 @pytest.mark.parametrize("top_k,top_p", [(50, 1.0), (0, 0.9), (50, 0.9)])
 def test_lists_and_the_sweep_agree(logits, top_k, top_p):
