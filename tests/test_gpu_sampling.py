@@ -207,6 +207,29 @@ def test_filters_on_a_narrow_logit_range(logits, top_k, top_p):
     say(f"  ok ({nf} filter-boundary sequences skipped, {nb} boundary, {nbm} differ)")
 
 
+@pytest.mark.parametrize("rows", ["few", "many"])
+@pytest.mark.parametrize("logits,offset", [("f32", 100.0), ("f32", 10000.0), ("f32", -100000.0), ("bf16", 100.0)])
+@pytest.mark.parametrize("top_k,top_p", [(0, 0.9), (0, 0.5), (50, 0.9)])
+def test_filters_with_an_offset_on_every_logit(rows, logits, offset, top_k, top_p):
+    """A constant on every logit leaves the distributions, and so top-p's masses,
+    what they are (here those of the logits as rounded with it): the row's
+    mass carries no rounding of the offset times log2(e)/T, in both widths of
+    the threshold kernel."""
+    B, V, gam = (6, 20000, (2, 5)) if rows == "few" else (40, 5000, (8, 8))
+    inp = level_inputs(small_shape(name=f"offset-{rows}", B=B, V=V, gamma=gam, seed=53), kv=False)
+    p, q = ((x + np.float32(offset)).astype(np.float32) for x in (inp.p_logits, inp.q_logits))
+    if logits == "bf16":
+        p, q = bf16_bits_from_f32(p), bf16_bits_from_f32(q)
+    say(f"offset {offset} {logits} {rows} rows top_k={top_k} top_p={top_p}")
+    got = run_accept(p, q, inp.drafts, inp.gamma, inp.u_acc, inp.u_res, temperature=0.8, top_k=top_k, top_p=top_p)
+    ref = oracle.accept_and_diverge(p, q, inp.drafts, inp.gamma, inp.u_acc, inp.u_res, temperature=0.8, top_k=top_k,
+                                    top_p=top_p)
+    assert got["status"] == ref["status"] == 0
+    nf, nb, nbm = _check_filtered(got, ref)
+    assert nf < B
+    say(f"  ok ({nf} filter-boundary sequences skipped, {nb} boundary, {nbm} differ)")
+
+
 def test_top_k_one_with_argmax_drafts_is_greedy_on_device():
     shape = small_shape(name="k1", B=8, V=12288, gamma=(2, 6), seed=44, logits="bf16")
     inp = level_inputs(shape, kv=False)
