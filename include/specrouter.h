@@ -162,12 +162,16 @@ int specrouter_verify_attention(const void* q, const void* k_cache, const void* 
  *               unchanged for a sequence with bad data
  * accept_prob, p_tok, q_tok, kl, tv: fp32 [B][gamma_max] or NULL each; entries
  *               j >= gamma_b (and all entries of a bad sequence) are NaN
- * workspace     device scratch of specrouter_accept_workspace_size() bytes (part
- *               of them room for what top-k / top-p keep: with less, such
- *               calls work through every logit instead); it must be
- *               zero-filled before its FIRST use and every call leaves
- *               it zero-filled again, whatever shape the next call has (each
- *               call clears every word it wrote)
+ * workspace     device scratch of specrouter_accept_workspace_size() bytes, which
+ *               grow with B, gamma_max and V: one workspace sized for the
+ *               largest call serves every smaller one. Most of them are room
+ *               for what top-k / top-p keep of each row; a call is accepted
+ *               with less (SR_EWORKSPACE only below what the rest of it needs)
+ *               and then works through every logit of the rows that keep more
+ *               than there is room for, whose floats may differ in the last
+ *               bits. It must be zero-filled before its FIRST use and every
+ *               call leaves it zero-filled again, whatever shape the next
+ *               call has (each call clears every word it wrote)
  * Logits must be finite or -inf, with |logit| / T < 2^23; a row that is
  * entirely -inf is not supported. Any V from 1 to 524281: rows need no
  * alignment, but the logits pointers and the batch strides (in bytes) must be
@@ -296,8 +300,9 @@ int specrouter_accept_and_rollback(const void* p_logits, int64_t p_batch_stride,
  * SPECROUTER_NOALLOC_SCRATCH_BYTES in device memory that the library owns,
  * one per device, resident until the process ends. The call allocates
  * nothing. It returns SR_ESCRATCH, before touching the device, when the
- * workspace this shape needs (specrouter_accept_workspace_size) exceeds the
- * array. The first call on a device also enqueues one clearing kernel on
+ * workspace this shape needs at least, without the room for what top-k / top-p
+ * keep, exceeds the array; where specrouter_accept_workspace_size() does not
+ * exceed it, the results are the same bits as with a caller's workspace. The first call on a device also enqueues one clearing kernel on
  * `stream` (and so does the first call after a call that failed with
  * SR_ELAUNCH); every call leaves the array ready for the next.
  * Calls on one device share its array: calls that overlap in time on one

@@ -2011,20 +2011,20 @@ int persistent_grid(const void* fn, long max_tasks, int Bl, int nc) {
   return grid < 1 ? 1 : (int)grid;
 }
 
-
 // What listing filtered rows takes behind the rest of the workspace: the mask
 // of swept rows, the row records, and lists of lcap entries per verifier row.
 // A list holds up to an eighth of the vocabulary, at most kListMax entries
-// (nucleus 0.9 of 128256 logits N(0, 9) at T = 0.7 keeps 400 to 750), and all
-// together keep the workspace within the fixed array of the no-allocation
-// call where the rest of it does, so that call takes the same shapes as
-// without lists and gives the same bits as a call with a workspace.
+// (nucleus 0.9 of 128256 logits N(0, 9) at T = 0.7 keeps 400 to 750): the size
+// query's bytes hold that for every row and grow with each of B, gamma_max and
+// V, so a workspace sized for the largest call lists alike in every smaller
+// one. With fewer bytes (an older size, the fixed array of the no-allocation
+// call and a large batch) the lists are as long as those bytes hold.
 struct ListLayout {
   size_t smask, rowst, lists, total;
   int lcap;  // 0: no room, no lists
 };
 
-ListLayout list_layout(int B, int gamma_max, int V, size_t base) {
+ListLayout list_layout(int B, int gamma_max, int V, size_t base, size_t bytes) {
   const size_t rows = (size_t)B * (gamma_max + 1);
   ListLayout L;
   L.smask = base;
@@ -2033,15 +2033,9 @@ ListLayout list_layout(int B, int gamma_max, int V, size_t base) {
   size_t cap = (size_t)((V / 8 + 63) / 64 * 64);
   if (cap < 64) cap = 64;
   if (cap > (size_t)kListMax) cap = kListMax;
-  if (base <= SPECROUTER_NOALLOC_SCRATCH_BYTES) {
-    const size_t left = SPECROUTER_NOALLOC_SCRATCH_BYTES > L.lists + 256 ? SPECROUTER_NOALLOC_SCRATCH_BYTES - L.lists - 256 : 0;
-    const size_t fit = left / (rows * sizeof(u32x2)) / 64 * 64;
-    if (fit < cap) cap = fit;
-  } else if (cap > 512) {
-    cap = 512;  // a very large batch: 4 KB per verifier row
-  }
+  L.total = L.lists + rows * cap * sizeof(u32x2);  // (cap is a multiple of 64: whole lines)
+  if (bytes < L.total) cap = bytes > L.lists ? (bytes - L.lists) / (rows * sizeof(u32x2)) / 64 * 64 : 0;
   L.lcap = (int)cap;
-  L.total = cap ? L.lists + align256(rows * cap * sizeof(u32x2)) : base;
   return L;
 }
 
@@ -2049,7 +2043,7 @@ ListLayout list_layout(int B, int gamma_max, int V, size_t base) {
 
 size_t accept_workspace_full(int B, int gamma_max, int V, int dtype) {
   const size_t base = accept_workspace_bytes(B, gamma_max, V, dtype);
-  return base == 0 ? 0 : list_layout(B, gamma_max, V, base).total;
+  return base == 0 ? 0 : list_layout(B, gamma_max, V, base, 0).total;
 }
 
 size_t accept_workspace_bytes(int B, int gamma_max, int V, int dtype) {
@@ -2086,9 +2080,8 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
   const int k_eff = top_k > 0 && top_k < V ? top_k : 0;
   const float p_eff = top_p < 1.f ? top_p : 1.f;
   const bool filt = !greedy && (k_eff > 0 || p_eff < 1.f);
-  // rows are listed when the workspace has the room that its size query asks for
-  const ListLayout LL = list_layout(B, gamma_max, V, plan.workspace_bytes);
-  const bool list = filt && LL.lcap > 0 && workspace_bytes >= LL.total;
+  const ListLayout LL = list_layout(B, gamma_max, V, plan.workspace_bytes, workspace_bytes);
+  const bool list = filt && LL.lcap > 0;
   // sequences in launches of at most kMaxSeqs (the row table)
   for (int b0 = 0; b0 < B; b0 += kMaxSeqs) {
     const int Bl = B - b0 < kMaxSeqs ? B - b0 : kMaxSeqs;

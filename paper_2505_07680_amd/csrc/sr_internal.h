@@ -293,8 +293,8 @@ struct AcceptPlan {
 
 int accept_plan(int B, int gamma_max, int V, int dtype, AcceptPlan* plan);
 // The workspace bytes an accept call of this shape needs (0: unsupported
-// shape), and those with which filtered rows can be listed (at least as
-// many); host arithmetic only, no device query.
+// shape), and those with which every filtered row can be listed (more); host
+// arithmetic only, no device query.
 size_t accept_workspace_bytes(int B, int gamma_max, int V, int dtype);
 size_t accept_workspace_full(int B, int gamma_max, int V, int dtype);
 

@@ -160,6 +160,27 @@ def test_noalloc_accept_refuses_oversized_shapes_before_the_device(lib):
     assert call(16, 5, 1000, dtype=7) == _lib.SR_EUNSUPPORTED
 
 
+@pytest.mark.parametrize("dtype", [_lib.SR_F32, _lib.SR_BF16])
+def test_accept_workspace_grows_with_every_size_and_has_room_for_lists(lib, dtype):
+    """A workspace sized for the largest call is large enough for every smaller
+    one, and has at least 64 entries of 8 bytes per verifier row beyond the
+    records (a 32-byte record and four 8-byte sums per 4096 logits)."""
+    size = lib.specrouter_accept_workspace_size
+    batches = list(range(1, 300)) + list(range(300, 1000, 7)) + [1023, 1024, 4096, 4097, 9000]
+    for V in (1, 7, 511, 513, 4096, 32000, 50257, 128256, 262144, 300000, 524281):
+        for G in (0, 1, 8, 16):
+            got = [size(B, G, V, dtype) for B in batches]
+            some = [g for g in got if g]  # (0: too many records for one launch)
+            assert some == got[: len(some)] and some == sorted(some)
+            for B, g in zip(batches, some):
+                assert g >= B * (G + 1) * (64 * (V // 4096) + 64 * 8)
+    for B in (1, 3, 64, 256, 713, 900):
+        got = [size(B, 8, V, dtype) for V in range(1, 300000, 997)]
+        assert got == sorted(got)
+        got = [size(B, G, 128256, dtype) for G in range(17)]
+        assert got == sorted(got)
+
+
 @no_device
 def test_chain_calls_reject_bad_host_arguments(lib):
     p = ctypes.c_void_p(4096)
