@@ -34,7 +34,7 @@
 //     ONE query, so the softmax max/sum need only two cross-lane steps;
 //   * the softmax reference of a row is raised to a tile's maximum only when
 //     that exceeds it by more than 2^8, so the output accumulators are rarely
-//     rescaled; where the plan has fewer splits than one workgroup per CU it
+//     rescaled; where fewer splits than one workgroup per CU take the least time it
 //     also moves within one binade with every tile (see next_ref and
 //     attention_plan), which rescales them by less than 2 each time;
 //   * P is rounded to bf16 in place: its accumulator layout is exactly the B
@@ -933,16 +933,15 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   const int per_cu = resident_per_cu((const void*)pick_split(D, plan->nq, plan->qg, plan->q_chunks, false), threads, 0);
   const long pairs = (long)B * Hkv * plan->q_chunks;
   const long target = (long)cus * per_cu;
-  // Splits: the count, up to one workgroup per CU, whose time is least. In
-  // units of a key's time in a workgroup (16 ns at D = 128, a CU's share of HBM):
-  // the keys of a split, times the workgroups the busiest CU gets, and the merge
-  // of each split's partial, 0.2 to 0.35 us or about 16 keys (32 at D = 64 with
-  // one query group, whose keys take less). One sequence of 2048 keys, 32/8 heads
-  // of 128, gamma 5: 24.8 us with the 32 splits that fill the CUs and the merge
-  // of before, 18.8 with the present merge, 16.6 with 11; 12 sequences of 2048,
-  // gamma 0: 28.8 us with 3 splits (288 workgroups for 256 CUs), 23.7 with 2.
+  // Splits: the count, up to one workgroup per CU, whose time is least for
+  // sequences of L_cap keys each. In units of a key's time in a workgroup (16 ns
+  // at D = 128, a CU's share of HBM): the keys of a split, times the workgroups
+  // the busiest CU gets, and the merge of each split's partial, 0.2 to 0.35 us
+  // or about 16 keys. One sequence of 2048 keys, 32/8 heads of 128, gamma 5:
+  // 24.8 us with the 32 splits that fill the CUs and the merge of before, 18.8
+  // with the present merge, 16.6 with 11.
   const long most = ((long)cus + pairs - 1) / pairs;
-  const long per_split = D == 64 && plan->qg == 1 ? 32 : 16;
+  constexpr long kPerSplit = 16;
   // With two query groups a softmax reference serves up to two tiles of a wave, so
   // where one workgroup per CU leaves a wave one tile (64 keys per split), the
   // splits stay that short (see follow below).
@@ -950,10 +949,34 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   const long least = plan->qg == 1 || L_cap > most * kTileKeys ? 1 : (L_cap + kTileKeys - 1) / kTileKeys;
   long splits = least, best = 0;
   for (long n = least; n <= most; ++n) {
-    const long t = (pairs * n + cus - 1) / cus * ((L_cap + n - 1) / n) + (n > 1 ? n * per_split : 0);
+    const long t = (pairs * n + cus - 1) / cus * ((L_cap + n - 1) / n) + (n > 1 ? n * kPerSplit : 0);
     if (n == least || t < best) {
       best = t;
       splits = n;
+    }
+  }
+  const bool few = splits < most;
+  // Lengths are not known here and may be anything up to L_cap. Where the pairs
+  // go into the CUs a few times with a remainder, that count is one workgroup
+  // per CU or fewer, and a ragged batch waits for its longest sequence alone on
+  // its CU. Two workgroups per CU instead (on long caches, where a merge is
+  // little, as many as fit), but for caches so short that the merge costs more
+  // than the balance gives, the more so where one split each leaves few CUs idle.
+  // (32/8 heads of 128, 256 to 8192 keys: 12 sequences 101 us with 2 splits, 58
+  // with 5; 17: 133 with 1, 75 with 3; 24: 170 with 1, 114 with 2. 2048 keys each:
+  // 17: 41.4 and 33.6; 24: 41.6 and 44.7; 31: 43 and 50. 512 keys each, 24: 11 and
+  // 12.) A single row block has fewer products per key and is near HBM's rate with
+  // fewer CUs; two query groups take a CU each, so their second workgroup only
+  // waits its turn, which pays with few splits of long caches.
+  const long whole = pairs < cus ? cus / pairs : 0;
+  if (whole >= 1 && cus % pairs != 0) {
+    const long busy = 10 * pairs * whole / cus;  // tenths of the CUs, the pairs taken a whole number of times
+    if (plan->qg == 1 && whole <= 7) {
+      const bool idle = whole > 1 || busy < (plan->nq > 1 ? 8 : 7);
+      if (L_cap >= 6000 && (plan->nq > 1 || !idle)) splits = target / pairs;
+      else if (L_cap >= 1000 && idle) splits = 2 * cus / pairs;
+    } else if (plan->qg > 1 && whole <= 2 && L_cap >= (busy < 6 ? 1500 : 3000)) {
+      splits = 2 * cus / pairs;
     }
   }
   // Bound a workgroup's keys, so the last workgroups of a ragged batch do not
@@ -977,7 +1000,7 @@ int attention_plan(int B, int gamma_max, int Hq, int Hkv, int D, int L_cap, Atte
   // them (64 to 8192 normal keys: 1.05e-3 off the 64-bit result with one tile
   // per wave, 1.5e-3 with three), so there the reference follows the tiles
   // (one such key per tile whatever the length: 1.05e-3 again).
-  plan->follow = splits < most ? 1 : 0;
+  plan->follow = few ? 1 : 0;
   // [arrival counters: B*Hkv*q_chunks, one per 128-byte line][partial o][partial (m, l)][order]
   const size_t counters = (size_t)B * Hkv * plan->q_chunks * kCounterStride * sizeof(uint32_t);
   plan->part_offset = counters;

@@ -387,6 +387,28 @@ def test_short_batches_round_no_more_than_one_tile_per_wave(Hq, Hkv, D, gam, key
     assert err < 1.2e-3
 
 
+# (sequence, kv head) pairs that do not divide an MI355X's 256 CUs: the plan
+# takes about two splits per CU (as many as fit on long caches) where a ragged
+# batch would wait for its longest sequence.
+@pytest.mark.parametrize("B,Hkv,G,D,gam,ctx", [
+    (17, 8, 4, 64, 5, (100, 1100)), (9, 8, 1, 128, 0, (30, 1100)), (31, 8, 4, 64, 5, (100, 1100)),
+    (5, 8, 4, 64, 3, (100, 6100)), (13, 17, 1, 64, 4, (100, 6100)), (17, 8, 8, 64, 8, (100, 1600)),
+], ids=lambda v: str(v).replace(" ", ""))
+def test_ragged_batches_whose_pairs_do_not_divide_the_cus(B, Hkv, G, D, gam, ctx):
+    shape = small_shape(name=f"ragged-{B}-{Hkv}-{G}-{D}", B=B, Hq=G * Hkv, Hkv=Hkv, D=D, gamma=(0, gam), ctx=ctx,
+                        V=1000, seed=B + Hkv + gam)
+    inp = level_inputs(shape, logits=False)
+    mask = _mask_holes(inp, 0.02, B)
+    got, st = run_attention(inp, mask=mask)
+    again, _ = run_attention(inp, mask=mask)
+    assert st == 0
+    np.testing.assert_array_equal(got, again)
+    seqs = [0, B // 2, int(np.argmax(inp.kv_len)), int(np.argmin(inp.kv_len))]
+    ref, _ = oracle.verify_attention(inp.q, inp.k, inp.v, inp.kv_len, inp.gamma, inp.scale, mask, seqs=seqs)
+    worst = check_attention(got, ref, seqs=seqs)
+    say(f"ragged B={B} heads={G * Hkv}/{Hkv} d{D}: worst relative L2 {worst:.2e}")
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("G,gam", [(1, 0), (8, 8)], ids=["1-row", "72-rows"])
 @pytest.mark.parametrize("course", ["falling", "rising", "zigzag"])
