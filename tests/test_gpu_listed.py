@@ -120,6 +120,49 @@ def test_masks_of_the_lowest_value_match_reference(logits, V, top_k, top_p):
     _check_filtered(got, ref)
 
 
+def _masked_rows(z, rng):
+    """Reshape the rows by kind: what constrained decoding and flat models leave."""
+    flat = z.reshape(-1, z.shape[-1])
+    V = flat.shape[1]
+    for i, row in enumerate(flat):
+        kind = i % 7
+        if kind == 1:  # the first half masked (a sample of the row's start sees nothing)
+            row[: V // 2] = -np.inf
+        elif kind == 2:  # three entries left
+            row[rng.permutation(V)[3:]] = -np.inf
+        elif kind == 3:  # 99% masked with a low but ordinary value
+            row[rng.random(V) < 0.99] = -1.0e4
+        elif kind == 4:  # two values
+            row[:] = rng.integers(0, 2, V).astype(np.float32)
+        elif kind == 5:  # one value
+            row[:] = 3.0
+        elif kind == 6:  # 97% masked, dealt in runs
+            row[(np.arange(V) // 64) % 33 != 0] = -np.inf
+    return z
+
+
+@pytest.mark.parametrize("logits", ["f32", "bf16"])
+@pytest.mark.parametrize("V,B", [(300, 6), (5003, 80), (50257, 6)])
+@pytest.mark.parametrize("top_k,top_p", [(50, 1.0), (0, 0.9), (50, 0.9), (2000, 0.9), (4500, 1.0)])
+def test_masked_and_tied_rows_match_reference(logits, V, B, top_k, top_p):
+    """Rows with fewer entries than top-k asks for, and rows whose entries
+    are mostly masks or equal, in both widths of the threshold kernel."""
+    inp = level_inputs(small_shape(name=f"masked-{logits}-{V}", B=B, V=V, gamma=(3, 4), seed=700 + V), kv=False)
+    rng = np.random.default_rng(V)
+    p = _masked_rows(inp.p_logits.astype(np.float32).copy(), rng)
+    q = _masked_rows(inp.q_logits.astype(np.float32).copy(), rng)
+    drafts = np.argmax(q + rng.gumbel(size=q.shape), axis=-1).astype(np.int32)
+    if logits == "bf16":
+        p, q = bf16_bits_from_f32(p), bf16_bits_from_f32(q)
+    say(f"masked rows {logits} V={V} B={B} top_k={top_k} top_p={top_p}")
+    got = run_accept(None, None, drafts, inp.gamma, inp.u_acc, inp.u_res, p_dev=_padded(p), q_dev=_padded(q),
+                     temperature=0.8, top_k=top_k, top_p=top_p)
+    ref = oracle.accept_and_diverge(p, q, drafts, inp.gamma, inp.u_acc, inp.u_res, temperature=0.8, top_k=top_k,
+                                    top_p=top_p)
+    assert got["status"] == ref["status"] == 0
+    _check_filtered(got, ref)
+
+
 @pytest.mark.parametrize("logits", ["f32", "bf16"])
 @pytest.mark.parametrize("top_k,top_p", [(50, 1.0), (0, 0.9), (50, 0.9)])
 def test_lists_and_the_sweep_agree(logits, top_k, top_p):
