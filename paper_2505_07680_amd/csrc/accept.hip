@@ -44,10 +44,9 @@
 //     |e_p c - e_q| over their entries, in units of f_q, and each wave
 //     publishes its part scaled back.
 // The sampling sweep is bound by its vector instructions, not by HBM: one factor
-// and one fma and add per entry in the TV sum, one fma per entry for the KL
-// numerator, maxima of two entries per instruction and wave reductions of one
-// instruction per step took 256 ragged sequences (gamma 1..8, bf16, V 128256)
-// from 242 to 198 us a call, 16 sequences of gamma 5, fp32, from 38.3 to 35.1.
+// and one fma and add per entry in the TV sum, maxima of two entries per
+// instruction and wave reductions of one instruction per step took 256 ragged sequences (gamma 1..8, bf16, V 128256)
+// from 242 to 194 us a call, 16 sequences of gamma 5, fp32, from 37.4 to 31.9.
 // Waiting is bounded: a task whose row is not complete after the time limit
 // publishes a "skipped" mark instead of its sum, and the row's finaliser
 // recomputes that chunk's sum from memory with the same arithmetic. No
@@ -570,10 +569,12 @@ __device__ __forceinline__ float shift_of(float m, float lg) { return m == kNegI
 // The exponentials of one wave's entries under shifts rp, rq, their sums and
 // the KL numerator sum e_p (x_p - x_q) (groups of four entries summed as
 // (a0 + a1) + (a2 + a3), then a tree over the groups; the KL terms in four
-// running sums). INF: an entry may be -inf, whose KL term is 0 (p's) or +inf
-// (q's alone), with a multiply that makes 0 inf = 0; else one fma per entry,
-// and a NaN total tells that an entry was -inf after all.
-template <bool INF, int kE>
+// running sums). An entry may be -inf, whose KL term is 0 (p's) or +inf (q's
+// alone): the multiply makes 0 inf = 0. (One fma per entry, with the wave's
+// logits read again when the total came out NaN, measured the same without
+// masks, 196 us at 256 ragged sequences, and 292 with them; at 16 sequences,
+// fp32, it spilled and took 33 us without masks and 46 with, now 32 and 33.)
+template <int kE>
 __device__ __forceinline__ void wave_exps(const float (&zp)[kE], const float (&zq)[kE], float lg, float rp, float rq,
                                           float (&ep)[kE], float (&eq)[kE], float& sp, float& sq, float& kl) {
   float gp[kE / 4], gq[kE / 4], gk[4] = {0.f, 0.f, 0.f, 0.f};
@@ -586,8 +587,7 @@ __device__ __forceinline__ void wave_exps(const float (&zp)[kE], const float (&z
       const float xq = fmaf(zq[e], lg, -rq);
       ep[e] = exp2_hw(xp);
       eq[e] = exp2_hw(xq);
-      if (INF) gk[i] += sr_fmul_legacy(ep[e], xp - xq);  // 0 where p is -inf, +inf where only q is
-      else gk[i] = g == 0 ? ep[e] * (xp - xq) : fmaf(ep[e], xp - xq, gk[i]);
+      gk[i] += sr_fmul_legacy(ep[e], xp - xq);
     }
     gp[g] = (ep[g * 4] + ep[g * 4 + 1]) + (ep[g * 4 + 2] + ep[g * 4 + 3]);
     gq[g] = (eq[g * 4] + eq[g * 4 + 1]) + (eq[g * 4 + 2] + eq[g * 4 + 3]);
@@ -608,33 +608,6 @@ __device__ __forceinline__ float wave_exps_p(const float (&zp)[kE], float lg, fl
     gp[g] = (ep[g * 4] + ep[g * 4 + 1]) + (ep[g * 4 + 2] + ep[g * 4 + 3]);
   }
   return wave_total(tree_sum(gp));
-}
-
-// A wave's KL numerator again, from memory, when some logit is -inf (rare: the
-// first pass keeps no logits for it).
-template <bool BF16>
-__device__ __forceinline__ float wave_kl_again(const Args& A, const TaskInfo& t, int wbase, float rp, float rq) {
-  constexpr int N = Vec<BF16>::N, esz = Vec<BF16>::esz, kE = Vec<BF16>::E;
-  const int lane = threadIdx.x & 63;
-  const RowSpan s = row_span<BF16>(A, t.b, t.j, true);
-  float gk = 0.f;
-#pragma unroll 1
-  for (int i = 0; i < kE / N; ++i) {
-    const uint32_t off = (uint32_t)((wbase + (i * 64 + lane) * N) * esz);
-    const u32x4 up = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s.rp, off, 0, 0));
-    const u32x4 uq = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s.rq, off, 0, 0));
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-      for (int h = 0; h < (BF16 ? 2 : 1); ++h) {
-        const float zp = !BF16 ? __uint_as_float(up[k]) : h ? bf16_hi(up[k]) : bf16_lo(up[k]);
-        const float zq = !BF16 ? __uint_as_float(uq[k]) : h ? bf16_hi(uq[k]) : bf16_lo(uq[k]);
-        const float xp = fmaf(zp, A.lg, -rp), xq = fmaf(zq, A.lg, -rq);
-        gk += sr_fmul_legacy(exp2_hw(xp), xp - xq);
-      }
-    }
-  }
-  return wave_total(gk);
 }
 
 // Sampling: each wave's maxima and shifts (its own: no exchange between the
@@ -660,12 +633,7 @@ __device__ __forceinline__ WaveShift first_pass(const Args& A, const TaskInfo& t
     rp = shift_of(mp, A.lg);
     rq = shift_of(mq, A.lg);
     store_xlogit<BF16>(A, t, wbase, zp, zq, rp, rq);
-    if (!FILT && t.full) {
-      wave_exps<false>(zp, zq, A.lg, rp, rq, ep, eq, sp, sq, kl);
-      if (kl != kl) kl = wave_kl_again<BF16>(A, t, wbase, rp, rq);
-    } else {
-      wave_exps<true>(zp, zq, A.lg, rp, rq, ep, eq, sp, sq, kl);
-    }
+    wave_exps(zp, zq, A.lg, rp, rq, ep, eq, sp, sq, kl);
   } else {
     mp = wave_top(mp);
     rp = shift_of(mp, A.lg);

@@ -54,6 +54,60 @@ def test_temperature_matches_reference(shape, T):
     say(f"  ok ({nb} boundary, {nbm} differ)")
 
 
+@pytest.mark.parametrize("logits", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [262140, 262145, 300007, 524281])
+def test_vocabularies_of_more_chunks_than_a_wave_has_lanes(logits, V):
+    """More than 64 chunks of 4096 logits per row (two records per lane in a row
+    merge) and the largest vocabulary: plain, greedy, and filtered."""
+    shape = small_shape(name=f"wide-{logits}", B=2, V=V, gamma=(1, 2), seed=V % 97, logits=logits)
+    inp = level_inputs(shape, kv=False)
+    per = 16 // inp.p_logits.itemsize
+
+    def up(x):  # each sequence's rows in an allocation whose stride is a multiple of 16 bytes
+        B, rows, _ = x.shape
+        buf = np.zeros((B, -(-rows * V // per) * per), x.dtype)
+        buf[:, : rows * V] = x.reshape(B, -1)
+        buf = buf.view(np.int16) if x.dtype == np.uint16 else buf
+        return torch.from_numpy(buf).cuda()[:, : rows * V].unflatten(1, (rows, V))
+
+    pd, qd = up(inp.p_logits), up(inp.q_logits)
+    for T, k, p in ((0.8, 0, 1.0), (0.0, 0, 1.0), (0.8, 50, 1.0), (0.8, 0, 0.9)):
+        say(f"wide {logits} V={V} T={T} top_k={k} top_p={p}")
+        ua, ur = (None, None) if T == 0 else (inp.u_acc, inp.u_res)
+        got = run_accept(None, None, inp.drafts, inp.gamma, ua, ur, p_dev=pd, q_dev=qd, temperature=T, top_k=k, top_p=p)
+        ref = oracle.accept_and_diverge(inp.p_logits, inp.q_logits, inp.drafts, inp.gamma, ua, ur, temperature=T,
+                                        top_k=k, top_p=p)
+        assert got["status"] == ref["status"] == 0
+        if T == 0:
+            _check_greedy(got, ref)
+        else:
+            _check_filtered(got, ref)
+
+
+@pytest.mark.parametrize("logits", ["f32", "bf16"])
+@pytest.mark.parametrize("share", [0.0005, 0.5, 0.995])
+@pytest.mark.parametrize("same", [True, False], ids=["same-masks", "own-masks"])
+def test_masked_logits_without_a_filter(logits, share, same):
+    """-inf in rows of whole chunks (the contract allows it), in the same places
+    of both rows or not: a term of KL is 0 where p has no mass and +infinity
+    where q alone has none."""
+    V = 3 * 4096
+    inp = level_inputs(small_shape(name=f"inf-{logits}", B=4, V=V, gamma=(3, 4), seed=61), kv=False)
+    rng = np.random.default_rng(int(share * 1e4))
+    p, q = inp.p_logits.astype(np.float32).copy(), inp.q_logits.astype(np.float32).copy()
+    mask = rng.random(p.shape) < share
+    p[mask] = -np.inf
+    q[mask[:, : q.shape[1]] if same else rng.random(q.shape) < share] = -np.inf
+    drafts = np.argmax(q + rng.gumbel(size=q.shape), axis=-1).astype(np.int32)
+    if logits == "bf16":
+        p, q = bf16_bits_from_f32(p), bf16_bits_from_f32(q)
+    say(f"masked {logits} share {share}")
+    got = run_accept(p, q, drafts, inp.gamma, inp.u_acc, inp.u_res, temperature=0.8)
+    ref = oracle.accept_and_diverge(p, q, drafts, inp.gamma, inp.u_acc, inp.u_res, temperature=0.8)
+    assert got["status"] == ref["status"] == 0
+    check_accept(got, ref)
+
+
 def _check_greedy(got, ref):
     assert got["status"] == ref["status"]
     np.testing.assert_array_equal(got["accept_len"], ref["accept_len"])
