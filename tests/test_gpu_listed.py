@@ -167,9 +167,11 @@ def test_masked_and_tied_rows_match_reference(logits, V, B, top_k, top_p):
 @pytest.mark.parametrize("top_k,top_p", [(50, 1.0), (0, 0.9), (50, 0.9)])
 def test_lists_and_the_sweep_agree(logits, top_k, top_p):
     """A workspace of the bytes that a call needs at least, without room for
-    lists, sends every row through the sweep: the same decisions, and floats
-    within the sweep's 32-bit sums of the lists' 64-bit ones (1e-6 of the
-    value; 1e-7 near zero). Both leave the workspace all zero."""
+    lists, sends every row through the sweep, and one with room for short
+    lists only those that keep more: the same decisions, and floats within the
+    sweep's 32-bit sums of the lists' 64-bit ones (1e-6 of the value; 1e-7 near
+    zero), but not the same bits: rows were listed. Each leaves the workspace
+    all zero."""
     V, B = 33000, 12
     inp, p, q, drafts = _inputs(V, logits, B, (2, 5), 77)
     code = sr.SR_BF16 if logits == "bf16" else sr.SR_F32
@@ -180,18 +182,22 @@ def test_lists_and_the_sweep_agree(logits, top_k, top_p):
     rows = B * (G + 1)
     up = lambda n: (n + 255) // 256 * 256  # noqa: E731
     least = up(rows * nc * 32) + up(rows * nc * 32) + up(rows * 16) + up(rows * 8) + 256
-    assert least < full.numel()
+    lists = up((B + 1) * 4) + up(rows * 2 * 16)  # the swept positions and the rows' sums; then 2048 entries per row
+    assert full.numel() == least + lists + rows * 2048 * 8
     args = (p, q, drafts, inp.gamma, inp.u_acc, inp.u_res)
     kw = dict(kv_len=inp.kv_len, temperature=0.8, top_k=top_k, top_p=top_p)
     a = run_accept(*args, bufs=bufs, **kw)
     assert int((full != 0).sum()) == 0
-    bufs.workspace = torch.zeros(least, dtype=torch.uint8, device="cuda")
-    b = run_accept(*args, bufs=bufs, **kw)
-    assert int((bufs.workspace != 0).sum()) == 0
-    for k in ("accept_len", "out_tokens", "new_len", "status"):
-        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
-    for k in ("accept_prob", "p_tok", "q_tok", "kl", "tv"):
-        np.testing.assert_allclose(a[k], b[k], rtol=1e-6, atol=1e-7, err_msg=k)
+    for room in (0, lists + rows * 64 * 8):
+        bufs.workspace = torch.zeros(least + room, dtype=torch.uint8, device="cuda")
+        b = run_accept(*args, bufs=bufs, **kw)
+        assert int((bufs.workspace != 0).sum()) == 0
+        for k in ("accept_len", "out_tokens", "new_len", "status"):
+            np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+        for k in ("accept_prob", "p_tok", "q_tok", "kl", "tv"):
+            np.testing.assert_allclose(a[k], b[k], rtol=1e-6, atol=1e-7, err_msg=k)
+        if room == 0:
+            assert any((a[k] != b[k])[~np.isnan(a[k])].any() for k in ("kl", "tv"))
     bufs.workspace = torch.zeros(least - 256, dtype=torch.uint8, device="cuda")
     with pytest.raises(RuntimeError):
         run_accept(*args, bufs=bufs, **kw)
