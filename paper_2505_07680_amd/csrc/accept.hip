@@ -43,10 +43,14 @@
 //     reciprocal estimate and two Newton steps); the lanes then sum
 //     |e_p c - e_q| over their entries, in units of f_q, and each wave
 //     publishes its part scaled back.
-// The sampling sweep is bound by its vector instructions, not by HBM: one factor
-// and one fma and add per entry in the TV sum, maxima of two entries per
-// instruction and wave reductions of one instruction per step took 256 ragged sequences (gamma 1..8, bf16, V 128256)
-// from 242 to 194 us a call, 16 sequences of gamma 5, fp32, from 37.4 to 31.9.
+// What bounds the sampling sweep: over many rows the chain of each task's
+// vector instructions, poll and barriers rather than HBM. At 256 ragged
+// sequences (gamma 1..8, bf16, V 128256) a wave issues 335 vector instructions
+// per task and the vector units are busy 57% of the time; over few rows it is
+// latency (16 sequences of gamma 5, fp32: 24%). One factor and one fma and add
+// per entry in the TV sum, maxima of two entries per instruction and wave
+// reductions of one instruction per step (440 instructions before) took the
+// former from 242 to 194 us a call, the latter from 37.4 to 31.9.
 // Waiting is bounded: a task whose row is not complete after the time limit
 // publishes a "skipped" mark instead of its sum, and the row's finaliser
 // recomputes that chunk's sum from memory with the same arithmetic. No
@@ -66,7 +70,8 @@
 // With top-k or top-p a kernel before the sweep (filter.inc) finds the rows'
 // thresholds. Rows that keep few entries are "listed" there (the entries of
 // the verifier row and both normalisers in the workspace): the sweep leaves
-// them out and the finish works from the lists, in 64 bits.
+// them out and the finish works from the lists: 32-bit exponentials with what
+// the rounding of their arguments left out added back, sums in 64 bits.
 //
 // Greedy decoding (T = 0) runs the same launches with chunk argmaxes in place
 // of the first pass and no TV step or waiting.
@@ -871,7 +876,9 @@ __device__ __forceinline__ double recip(double s) {
 // at most 1 an entry took three instructions and the factors about fifty per
 // wave.) Rows with equal factors have c = 1 and subtract exactly. c is held
 // to 2^60 times S_q/S_p: beyond, e takes the rest, and the q side is then too
-// large by that power of two, below 2^-50 of the p side.
+// large by that power of two, yet below 2^-29 of the wave's p side (S_q >= 1/2,
+// S_p <= 2^19, an e_p >= 1/2, 1024 entries with e_q <= 1). In a wave where p has
+// no entry the q side is below 2^-49 of the whole either way.
 struct TvPar {
   float c;
   int e;
@@ -1473,8 +1480,9 @@ __device__ __forceinline__ ListRow list_row(const Args& A, int row, bool pair) {
   return L;
 }
 
-// Row j of sequence b (one wave) from its list: TV, KL, p(x), q(x) and a, all
-// in 64 bits. The p row's kept entries come from the list, q's logits at the
+// Row j of sequence b (one wave) from its list: TV, KL, p(x), q(x) and a, in 64
+// bits but for the exponentials (ListEnt) and the product of each KL term's
+// rounded exponential and arguments. The p row's kept entries come from the list, q's logits at the
 // same places from memory; what q keeps elsewhere is its sum less what was met.
 template <bool BF16>
 __device__ RowOut finalize_listed(const Args& A, int b, int j, int gam) {

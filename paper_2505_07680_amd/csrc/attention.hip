@@ -161,7 +161,9 @@ __device__ __forceinline__ float next_ref(float mt, float m_run, bool grow) {
 }
 
 // Waves per SIMD the register allocation must allow: three for one row block
-// (168 registers), else two (256).
+// (168 registers), else two (256). Two groups of three blocks at D = 128 use all
+// 256 and keep three or four values in scratch that the ring's loop reads back
+// (six loads per round of four tiles).
 template <int D, int NQ, int QG, bool NT, bool FOLLOW>
 __global__ void __launch_bounds__(Shape<QG>::kThreads, NQ == 1 && QG == 1 ? 3 : 2)
 attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
