@@ -302,9 +302,10 @@ int specrouter_accept_and_rollback(const void* p_logits, int64_t p_batch_stride,
  * nothing. It returns SR_ESCRATCH, before touching the device, when the
  * workspace this shape needs at least, without the room for what top-k / top-p
  * keep, exceeds the array; where specrouter_accept_workspace_size() does not
- * exceed it, the results are the same bits as with a caller's workspace. The first call on a device also enqueues one clearing kernel on
- * `stream` (and so does the first call after a call that failed with
- * SR_ELAUNCH); every call leaves the array ready for the next.
+ * exceed it, the results are the same bits as with a caller's workspace. The
+ * first call on a device also enqueues one clearing kernel on `stream` (and so
+ * does the first call after a call that failed with SR_ELAUNCH); every call
+ * leaves the array ready for the next.
  * Calls on one device share its array: calls that overlap in time on one
  * device (different streams, threads or processes' graphs) race and give
  * wrong results; serialise them, e.g. on one stream.
