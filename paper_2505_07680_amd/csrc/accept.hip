@@ -195,7 +195,7 @@ struct Args {
   float* thr;        // [B][gmax+1][2] top-k / top-p thresholds of the p and q rows, or NULL
   // rows that top-k / top-p leave few entries of (NULL: no such rows are listed)
   uint32_t* smask;   // [B] bit j: the sweep takes position j (its rows are not listed)
-  uint32_t* swany;   // non-zero: some bit of smask is set (any launch of the call)
+  uint32_t* swany;   // non-zero: some bit of smask is set
   RowStat* rowst;    // [B][gmax+1][2] the listed rows, p then q
   u32x2* lists;      // [B][gmax+1][lcap] the kept entries of the p rows: (value, index), ascending index
   int lcap;
@@ -1994,17 +1994,19 @@ int persistent_grid(const void* fn, long max_tasks, int Bl, int nc) {
 // query's bytes hold that for every row and grow with each of B, gamma_max and
 // V, so a workspace sized for the largest call lists alike in every smaller
 // one. With fewer bytes (an older size, the fixed array of the no-allocation
-// call and a large batch) the lists are as long as those bytes hold.
+// call and a large batch) the lists are as long as those bytes hold. They are
+// one launch's: the next of the call finds them cleared.
 struct ListLayout {
   size_t smask, rowst, lists, total;
   int lcap;  // 0: no room, no lists
 };
 
 ListLayout list_layout(int B, int gamma_max, int V, size_t base, size_t bytes) {
-  const size_t rows = (size_t)B * (gamma_max + 1);
+  const size_t seqs = B < kMaxSeqs ? B : kMaxSeqs;
+  const size_t rows = seqs * (gamma_max + 1);
   ListLayout L;
   L.smask = base;
-  L.rowst = L.smask + align256(((size_t)B + 1) * sizeof(uint32_t));
+  L.rowst = L.smask + align256((seqs + 1) * sizeof(uint32_t));
   L.lists = L.rowst + align256(rows * 2 * sizeof(RowStat));
   size_t cap = (size_t)((V / 8 + 63) / 64 * 64);
   if (cap < 64) cap = 64;
@@ -2089,10 +2091,10 @@ int launch_accept(const void* p_logits, int64_t p_stride, const void* q_logits, 
     A.tva = (double*)(ws + L.tva) + r0 * nc * kWaves;
     A.xlogit = (float*)(ws + L.xlogit) + r0 * 4;
     A.thr = filt ? (float*)(ws + L.thr) + r0 * 2 : nullptr;
-    A.smask = list ? (uint32_t*)(ws + LL.smask) + b0 : nullptr;
-    A.swany = list ? (uint32_t*)(ws + LL.smask) + B : nullptr;
-    A.rowst = list ? (RowStat*)(ws + LL.rowst) + r0 * 2 : nullptr;
-    A.lists = list ? (u32x2*)(ws + LL.lists) + r0 * LL.lcap : nullptr;
+    A.smask = list ? (uint32_t*)(ws + LL.smask) : nullptr;
+    A.swany = list ? A.smask + (B < kMaxSeqs ? B : kMaxSeqs) : nullptr;
+    A.rowst = list ? (RowStat*)(ws + LL.rowst) : nullptr;
+    A.lists = list ? (u32x2*)(ws + LL.lists) : nullptr;
     A.lcap = list ? LL.lcap : 0;
     A.status = status;
     A.rb_kv = rollback ? rollback->kv_len + b0 : nullptr;

@@ -164,7 +164,8 @@ def test_noalloc_accept_refuses_oversized_shapes_before_the_device(lib):
 def test_accept_workspace_grows_with_every_size_and_has_room_for_lists(lib, dtype):
     """A workspace sized for the largest call is large enough for every smaller
     one, and has at least 64 entries of 8 bytes per verifier row beyond the
-    records (a 32-byte record and four 8-byte sums per 4096 logits)."""
+    records (a 32-byte record and four 8-byte sums per 4096 logits) for the
+    4096 sequences of a launch."""
     size = lib.specrouter_accept_workspace_size
     batches = list(range(1, 300)) + list(range(300, 1000, 7)) + [1023, 1024, 4096, 4097, 9000]
     for V in (1, 7, 511, 513, 4096, 32000, 50257, 128256, 262144, 300000, 524281):
@@ -173,7 +174,7 @@ def test_accept_workspace_grows_with_every_size_and_has_room_for_lists(lib, dtyp
             some = [g for g in got if g]  # (0: too many records for one launch)
             assert some == got[: len(some)] and some == sorted(some)
             for B, g in zip(batches, some):
-                assert g >= B * (G + 1) * (64 * (V // 4096) + 64 * 8)
+                assert g >= (G + 1) * (B * 64 * (V // 4096) + min(B, 4096) * 64 * 8)
     for B in (1, 3, 64, 256, 713, 900):
         got = [size(B, 8, V, dtype) for V in range(1, 300000, 997)]
         assert got == sorted(got)

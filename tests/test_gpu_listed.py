@@ -94,6 +94,28 @@ def test_listed_rows_match_reference(logits, V, top_k, top_p):
         say(f"  ok ({nf} filter-boundary skipped, {nb} boundary, {nbm} differ)")
 
 
+@pytest.mark.parametrize("top_k,top_p", [(20, 1.0), (0, 0.9)])
+def test_lists_over_several_launches(top_k, top_p):
+    """More sequences than one launch takes: the lists' room is one launch's and
+    is found cleared by the next, whose sequences are listed, swept or both."""
+    V, B = 300, 4100
+    inp, p, q, drafts = _inputs(V, "f32", B, (0, 2), 977)
+    say(f"lists over two launches top_k={top_k} top_p={top_p}")
+    bufs = sr.AcceptBuffers(B, p.shape[1] - 1, V, sr.SR_F32)
+    args = (None, None, drafts, inp.gamma, inp.u_acc, inp.u_res)
+    kw = dict(p_dev=_padded(p), q_dev=_padded(q), bufs=bufs, temperature=0.8, top_k=top_k, top_p=top_p)
+    got = run_accept(*args, **kw)
+    again = run_accept(*args, **kw)
+    assert int((bufs.workspace != 0).sum()) == 0
+    for k in ("accept_len", "out_tokens", "accept_prob", "kl", "tv"):
+        np.testing.assert_array_equal(got[k], again[k], err_msg=k)
+    seqs = list(range(0, 40)) + list(range(4080, 4100))
+    sub = [np.asarray(x)[seqs] for x in (p, q, drafts, inp.gamma, inp.u_acc, inp.u_res)]
+    ref = oracle.accept_and_diverge(*sub, temperature=0.8, top_k=top_k, top_p=top_p)
+    assert got["status"] == ref["status"] == 0
+    _check_filtered({k: v[seqs] if isinstance(v, np.ndarray) else v for k, v in got.items()}, ref)
+
+
 LOWEST = {"f32": np.float32(-3.4028234663852886e38), "bf16": np.float32(-3.3895313892515355e38)}
 
 
