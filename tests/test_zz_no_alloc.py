@@ -92,3 +92,20 @@ def test_noalloc_matches_workspace_call(label, big, small, sampling):
                                             inp.u_res, kv_len=inp.kv_len)
             check_accept(got, ref)
         assert got["status"] == 0
+
+
+def test_noalloc_with_room_for_shorter_lists():
+    """A filtered call whose lists outgrow the fixed array: the same decisions
+    as with a caller's workspace, floats within the sweep's 32-bit sums of the
+    lists' (1e-6; 1e-7 near zero), and the same bits on a second call."""
+    inp = level_inputs(small_shape(name="noalloc-lists", B=200, V=16000, gamma=(6, 8), seed=79), kv=False)
+    cap = int(inp.kv_len.max()) + 8
+    assert sr.specrouter_accept_workspace_size(200, 8, 16000, sr.SR_F32) > 16 << 20
+    say("noalloc, lists that outgrow the array")
+    kw = dict(temperature=0.7, top_p=0.9)
+    want, got, again = _run(inp, False, cap, **kw), _run(inp, True, cap, **kw), _run(inp, True, cap, **kw)
+    _same(got, again)
+    for n in ("accept_len", "out_tokens", "new_len", "kv", "mask", "phys", "status"):
+        np.testing.assert_array_equal(got[n], want[n], err_msg=n)
+    for n in ("accept_prob", "p_tok", "q_tok", "kl", "tv"):
+        np.testing.assert_allclose(got[n], want[n], rtol=1e-6, atol=1e-7, err_msg=n)
